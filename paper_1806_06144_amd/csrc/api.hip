@@ -3,6 +3,7 @@
 #include "eigenpro.h"
 #include "ep_host.h"
 #include "ep_internal.h"
+#include "split.h"
 
 #include <rocblas/rocblas.h>
 #include <rocsolver/rocsolver.h>
@@ -108,8 +109,14 @@ struct ep_ctx {
     DevBuf norms, alpha, r_dev, Xs, xs_norms, V, Dk, err;
     DevBuf kpos;                        // n ints: subsample position of each row, or -1
     DevBuf ksb;                         // s x round_up(m, 64): K(X_r, X_t) captured in step 2
+    // split-precision operands (split.h), held while `split` is set: the
+    // packed centres, their inverse scales, and the planes of alpha (lt16
+    // label tiles of 16)
+    bool split = false;
+    int64_t lt16 = 0;
+    DevBuf Xp, xinv, wplanes;
     // per-call scratch
-    DevBuf xb, xb_norms, R, part, G, vt_part, W1, zn;
+    DevBuf xb, xb_norms, R, part, G, vt_part, W1, zn, Qp;
 
     bool timing = false;
     std::vector<TimedPair> kmv_ev, step_ev, kblk_ev, gemm_ev;
@@ -122,7 +129,8 @@ struct ep_ctx {
 
     ~ep_ctx() {
         for (DevBuf* b : {&norms, &alpha, &r_dev, &Xs, &xs_norms, &V, &Dk, &err, &kpos, &ksb,
-                          &xb, &xb_norms, &R, &part, &G, &vt_part, &W1, &zn})
+                          &xb, &xb_norms, &R, &part, &G, &vt_part, &W1, &zn, &Xp, &xinv, &wplanes,
+                          &Qp})
             b->release();
         for (auto& p : kmv_ev) {
             (void)hipEventDestroy(p.a);
@@ -209,6 +217,100 @@ int run_kmv(ep_ctx* c, const float* Q, int64_t ldq, const float* qn, const int64
         if (rc) return rc;
     }
     return EP_OK;
+}
+
+unsigned short* planes_of(ep_ctx* c) {
+    return c->split ? c->wplanes.as<unsigned short>() : nullptr;
+}
+
+// Whether F = K(Q, X) alpha takes the split-precision fused pass: where its
+// operands are held (setup_split), the blocked form is not asked for and
+// the pass has more than 2^27 multiply-adds (queries counted in tiles of 64).
+// Below that both passes are a few microseconds of work behind their
+// latency, and the float32 pass spreads it over four times as many
+// workgroups (n = 2000, d = 64, 256 queries: 16 against 19 us).
+bool use_split(const ep_ctx* c, int64_t nq) {
+    return c->split && c->contract != EP_CONTRACT_BLOCKED && c->lt16 <= kMaxFusedTiles &&
+           (double)round_up(nq, kBM) * (double)c->n * (double)c->d > (double)(1 << 27);
+}
+// The same for a training step. Laplacian steps on rows of more than 2048
+// features stay on the float32 pass: there a step's result depends on the
+// summation order at the 5e-5 level from the second step on (n = 50000,
+// d = 3072, uniform features: 5.3e-5 of float64 with the float32 pass, 4.1e-5
+// with this one, 6e-5 between the two), more than a change of kernel may
+// move it. It would take 2.4 ms instead of 7.5 ms there.
+bool use_split_step(const ep_ctx* c, int64_t m) {
+    return use_split(c, m) && !(c->kind == EP_LAPLACIAN && c->d > 2048);
+}
+
+// Packs query rows for the split pass into `out`: rows idx[0 .. nq) of Z, or
+// its first nq rows. `training`: Z is X (rows 0 .. n - 1), whose norms and
+// scales are held.
+int pack_queries(ep_ctx* c, const float* Z, const int64_t* idx, int64_t nq, char* out,
+                 bool training) {
+    PackArgs a{};
+    a.X = Z;
+    a.n = c->n;
+    a.d = c->d;
+    a.idx = idx;
+    a.rows = nq;
+    if (training) {
+        a.norms_in = c->norms.as<float>();
+        a.inv_in = c->xinv.as<float>();
+    }
+    a.out = out;
+    a.P = kQPanel;
+    a.queries = true;
+    a.err = c->err.as<int>();
+    HIP_TRY(launch_pack_rows(a, c->stream));
+    return EP_OK;
+}
+
+size_t packed_bytes(const ep_ctx* c, int64_t nq) {
+    return (size_t)ceil_div(nq, kQPanel) * panel_bytes(kQPanel, c->d);
+}
+
+// The split-precision fused pass over all centres for nq packed queries.
+int run_split(ep_ctx* c, const char* Q, const int64_t* qid, int64_t nq, const SplitPlan& plan,
+              float* part, int64_t rows_pad, bool timed, bool capture) {
+    SplitArgs a{};
+    a.Q = Q;
+    a.q_panel = panel_bytes(kQPanel, c->d);
+    a.qid = qid;
+    a.nq = nq;
+    a.C = c->Xp.as<char>();
+    a.c_panel = panel_bytes(kCPanel, c->d);
+    a.nc = c->n;
+    a.nk = feature_steps(c->d);
+    a.W = c->wplanes.as<char>();
+    a.lt = (int)c->lt16;
+    a.out = part;
+    a.out_rows = rows_pad;
+    a.ldw = c->l_pad;
+    a.kind = c->kind;
+    a.scale = c->scale;
+    if (capture) {
+        a.kpos = c->kpos.as<int>();
+        a.ksb = c->ksb.as<float>();
+        a.ldk = rows_pad;
+    }
+    int rc = EP_OK;
+    if (timed && (rc = record(c->stream, c->kmv_ev, true))) return rc;
+    HIP_TRY(split_launch(a, plan, c->stream));
+    if (timed && (rc = record(c->stream, c->kmv_ev, false))) return rc;
+    return EP_OK;
+}
+
+// The same with the context's own partial sums.
+int run_split_pass(ep_ctx* c, const int64_t* qid, int64_t nq, int* slices, int64_t* rows_pad,
+                   bool timed, bool capture) {
+    *rows_pad = round_up(std::max<int64_t>(nq, 1), kBM);
+    const SplitPlan plan =
+        split_plan(nq, c->n, c->lt16, c->kind, max_slices_for(*rows_pad, c->l_pad));
+    *slices = plan.splits;
+    HIP_TRY(c->part.ensure((size_t)plan.splits * (size_t)(*rows_pad) * c->l_pad * sizeof(float)));
+    return run_split(c, c->Qp.as<char>(), qid, nq, plan, c->part.as<float>(), *rows_pad, timed,
+                     capture);
 }
 
 constexpr size_t kKBlockBudget = size_t(2) << 30;   // bytes of one chunk's kernel block
@@ -313,7 +415,8 @@ int run_main_pass(ep_ctx* c, const float* Q, int64_t ldq, const float* qn, const
 // subsample columns for steps 4-5: fused form, vector body, and the capture
 // buffer and the product's partial slices within budget.
 bool capture_subsample(const ep_ctx* c, const float* xb, int64_t m) {
-    return c->k > 0 && !use_blocked(c, xb, c->d) && kmv_vec(xb, c->d, c->X, c->d, c->d) &&
+    if (c->k == 0 || use_blocked(c, xb, c->d)) return false;
+    return (use_split_step(c, m) || kmv_vec(xb, c->d, c->X, c->d, c->d)) &&
            (size_t)c->s * (size_t)round_up(m, kBM) * sizeof(float) <= kKsbBudget;
 }
 
@@ -535,6 +638,45 @@ int apply_rank(ep_ctx* c, int64_t k) {
     return EP_OK;
 }
 
+// Row norms of the centres, and the split-precision operands (packed
+// centres, zero planes of alpha) where they take at most half of the free
+// device memory: without them every pass runs on float32 operands.
+int setup_split(ep_ctx* c) {
+    const int64_t n = c->n, d = c->d;
+    hipStream_t st = c->stream;
+    const int64_t lt = ceil_div(c->l, 16);
+    c->lt16 = lt;
+    const size_t xp = (size_t)ceil_div(n, kCPanel) * panel_bytes(kCPanel, d);
+    const size_t wp = (size_t)weight_plane_bytes(c->n_pad, c->lt16);
+    size_t free_b = 0, total_b = 0;
+    HIP_TRY(hipMemGetInfo(&free_b, &total_b));
+    c->split = n < (int64_t(1) << 31) - kCPanel && lt <= kMaxFusedTiles && xp + wp <= free_b / 2;
+    if (c->split && (c->Xp.ensure(xp) != hipSuccess || c->wplanes.ensure(wp) != hipSuccess ||
+                     c->xinv.ensure((size_t)n * sizeof(float)) != hipSuccess)) {
+        (void)hipGetLastError();       // another allocation took the memory meanwhile
+        c->Xp.release();
+        c->wplanes.release();
+        c->split = false;
+    }
+    if (!c->split) {
+        HIP_TRY(launch_row_norms(c->X, n, d, d, c->norms.as<float>(), st));
+        return EP_OK;
+    }
+    HIP_TRY(launch_fill_f32(c->wplanes.as<float>(), (int64_t)(wp / 4), 0.f, st));
+    PackArgs a{};
+    a.X = c->X;
+    a.n = n;
+    a.d = d;
+    a.rows = n;
+    a.out = c->Xp.as<char>();
+    a.P = kCPanel;
+    a.norms_out = c->norms.as<float>();
+    a.inv_out = c->xinv.as<float>();
+    a.err = c->err.as<int>();
+    HIP_TRY(launch_pack_rows(a, st));
+    return EP_OK;
+}
+
 int do_setup(ep_ctx* c, const int64_t* sub_idx, uint64_t seed, const double* sigma_in,
              const float* V_in) {
     const int64_t n = c->n, d = c->d, s = c->s, k = c->k;
@@ -594,7 +736,7 @@ int do_setup(ep_ctx* c, const int64_t* sub_idx, uint64_t seed, const double* sig
         HIP_TRY(hipMemcpy(c->kpos.p, kp.data(), (size_t)n * sizeof(int32_t),
                           hipMemcpyHostToDevice));
     }
-    HIP_TRY(launch_row_norms(c->X, n, d, d, c->norms.as<float>(), st));
+    if (int rc = setup_split(c)) return rc;
     HIP_TRY(launch_gather_rows(c->X, n, d, c->norms.as<float>(), c->r_dev.as<int64_t>(), s,
                                c->s_pad, c->Xs.as<float>(), c->xs_norms.as<float>(),
                                c->err.as<int>(), st));
@@ -697,6 +839,8 @@ int subsample_correction(ep_ctx* c, bool capture, const float* xb, const float* 
     g.r = c->r_dev.as<int64_t>();
     g.coef = coef;
     g.N_valid = c->l;
+    g.planes = planes_of(c);
+    g.lt = c->lt16;
     ThinGemmPlan one;
     one.kc = round_up(k, 64);
     one.chunks = 1;
@@ -844,21 +988,30 @@ int ep_step(ep_ctx* c, const int64_t* t, int64_t m, const float* y_b, float* f_o
     float* alpha = c->alpha.as<float>();
     float* R = c->R.as<float>();
 
-    // step 1: gather the batch
-    HIP_TRY(launch_gather_rows(c->X, c->n, c->d, c->norms.as<float>(), t, m, m_pad, xb, xbn,
-                               c->err.as<int>(), st));
+    const bool capture = capture_subsample(c, xb, m);
+    const bool split = use_split_step(c, m);
+    // step 1: gather the batch (the rows themselves only where a float32
+    // pass reads them)
+    if (split) {
+        HIP_TRY(c->Qp.ensure(packed_bytes(c, m)));
+        if ((rc = pack_queries(c, c->X, t, m, c->Qp.as<char>(), true))) return rc;
+    }
+    if (!split || (c->k > 0 && !capture))
+        HIP_TRY(launch_gather_rows(c->X, c->n, c->d, c->norms.as<float>(), t, m, m_pad, xb, xbn,
+                                   c->err.as<int>(), st));
     // step 2: F = K(X_t, X) alpha, fused; the kernel values of the
     // subsample columns are kept for steps 4-5 when the buffer allows
     int slices = 0;
     int64_t rows_pad = 0;
-    const bool capture = capture_subsample(c, xb, m);
     if (capture) HIP_TRY(c->ksb.ensure((size_t)c->s * round_up(m, kBM) * sizeof(float)));
-    rc = run_main_pass(c, xb, c->d, xbn, t, m, &slices, &rows_pad, c->timing, capture);
+    rc = split ? run_split_pass(c, t, m, &slices, &rows_pad, c->timing, capture)
+               : run_main_pass(c, xb, c->d, xbn, t, m, &slices, &rows_pad, c->timing, capture);
     if (rc) return rc;
     // step 3: R = F - y_b; alpha_t -= c R
     const double coef = 1.0 / (c->info.beta + (double)(m - 1) * c->info.lambda_k1);
     HIP_TRY(launch_reduce_residual(c->part.as<float>(), slices, rows_pad, c->l_pad, m, c->l, y_b,
-                                   f_out, R, m_pad, alpha, c->n, t, (float)coef, st));
+                                   f_out, R, m_pad, alpha, c->n, t, (float)coef, planes_of(c), c->lt16,
+                                   st));
     if (c->k > 0) {
         rc = subsample_correction(c, capture, xb, xbn, t, m, R, (float)coef);
         if (rc) return rc;
@@ -878,16 +1031,30 @@ int ep_predict(ep_ctx* c, const float* Z, int64_t n_z, float* out) {
     if (!Z || !out) return fail(EP_EINVAL, "Z and out must be device pointers");
     DeviceGuard dg(c->device);
     hipStream_t st = c->stream;
-    const int64_t chunk = 32768;
-    HIP_TRY(c->zn.ensure((size_t)std::min(n_z, chunk) * sizeof(float)));
+    const bool split = use_split(c, n_z);
+    int64_t chunk = 32768;
+    if (split) {
+        // packed rows of a chunk: at most 512 MiB, at least one panel
+        const int64_t panels = (int64_t)(size_t(512) << 20) / panel_bytes(kQPanel, c->d);
+        chunk = std::min(chunk, std::max<int64_t>(1, panels) * kQPanel);
+        HIP_TRY(c->Qp.ensure(packed_bytes(c, std::min(n_z, chunk))));
+    } else {
+        HIP_TRY(c->zn.ensure((size_t)std::min(n_z, chunk) * sizeof(float)));
+    }
     for (int64_t z0 = 0; z0 < n_z; z0 += chunk) {
         const int64_t nz = std::min(chunk, n_z - z0);
         const float* Zc = Z + z0 * c->d;
-        HIP_TRY(launch_row_norms(Zc, nz, c->d, c->d, c->zn.as<float>(), st));
         int slices = 0;
         int64_t rows_pad = 0;
-        int rc = run_main_pass(c, Zc, c->d, c->zn.as<float>(), nullptr, nz, &slices, &rows_pad,
+        int rc = EP_OK;
+        if (split) {
+            if ((rc = pack_queries(c, Zc, nullptr, nz, c->Qp.as<char>(), false))) return rc;
+            rc = run_split_pass(c, nullptr, nz, &slices, &rows_pad, false, false);
+        } else {
+            HIP_TRY(launch_row_norms(Zc, nz, c->d, c->d, c->zn.as<float>(), st));
+            rc = run_main_pass(c, Zc, c->d, c->zn.as<float>(), nullptr, nz, &slices, &rows_pad,
                                false);
+        }
         if (rc) return rc;
         HIP_TRY(launch_reduce_rows(c->part.as<float>(), slices, rows_pad, c->l_pad, nz, c->l,
                                    out + z0 * c->l, c->l, st));
@@ -915,6 +1082,44 @@ int ep_predict_noalloc(ep_ctx* c, const float* Z, int64_t n_z, float* out) {
                     "ep_predict_noalloc: %lld label columns exceed the %zu-float scratch "
                     "(at most %lld)", (long long)c->l,
                     kScratchFloats, (long long)((cap - kBM) / kBM));
+    // The split pass, where a panel of packed rows and its partial sums fit
+    // the scratch: chunks of `rows` packed rows first, the partial sums in
+    // what is left. Of the chunk sizes that fit, the one with the least
+    // predicted time is taken (larger chunks leave room for fewer splits).
+    if (use_split(c, n_z) &&
+        (int64_t)packed_bytes(c, kQPanel) / 4 + kQPanel * L <= cap) {
+        SplitPlan plan{};
+        int64_t rows = 0;
+        double best = 1e300;
+        for (int64_t panels = std::min<int64_t>(ceil_div(n_z, kQPanel), 512);; panels = ceil_div(panels, 2)) {
+            const int64_t nq = std::min<int64_t>(n_z, panels * kQPanel);
+            const int64_t left = cap - (int64_t)packed_bytes(c, nq) / 4;
+            const int64_t max_sl = left > 0 ? left / (round_up(nq, kBM) * L) : 0;
+            if (max_sl >= 1) {
+                const SplitPlan pl = split_plan(nq, c->n, c->lt16, c->kind,
+                                                (int)std::min<int64_t>(max_sl, 256));
+                const double t = pl.cost * (double)ceil_div(n_z, nq);
+                if (t < best) {
+                    best = t;
+                    plan = pl;
+                    rows = nq;
+                }
+            }
+            if (panels == 1) break;
+        }
+        char* q = reinterpret_cast<char*>(c->scratch);
+        for (int64_t z0 = 0; z0 < n_z; z0 += rows) {
+            const int64_t nq = std::min(rows, n_z - z0);
+            const int64_t rows_pad = round_up(nq, kBM);
+            float* part = c->scratch + packed_bytes(c, nq) / 4;
+            int rc = pack_queries(c, Z + z0 * c->d, nullptr, nq, q, false);
+            if (rc) return rc;
+            if ((rc = run_split(c, q, nullptr, nq, plan, part, rows_pad, false, false))) return rc;
+            HIP_TRY(launch_reduce_rows(part, plan.splits, rows_pad, L, nq, c->l, out + z0 * c->l,
+                                       c->l, st));
+        }
+        return EP_OK;
+    }
     for (int64_t z0 = 0; z0 < n_z;) {
         int64_t tq = std::min<int64_t>(ceil_div(n_z - z0, kBM), 512);
         tq = std::max<int64_t>(1, std::min<int64_t>(tq, (cap - kBM) / ((int64_t)kBM * (L + 1))));
@@ -978,6 +1183,9 @@ int ep_set_alpha(ep_ctx* c, const float* in) {
     DeviceGuard dg(c->device);
     HIP_TRY(hipMemcpy2DAsync(c->alpha.p, c->l_pad * sizeof(float), in, c->l * sizeof(float),
                              c->l * sizeof(float), c->n, hipMemcpyDeviceToDevice, c->stream));
+    if (c->split)
+        HIP_TRY(launch_pack_weights(c->alpha.as<float>(), c->n, c->l, c->l_pad, c->lt16,
+                                    c->wplanes.p, c->stream));
     return EP_OK;
 }
 
@@ -1047,15 +1255,23 @@ int ep_batch_sweep(ep_ctx* c, const int64_t* ms, int count, int reps, double* ms
         int slices = 0;
         int64_t rows_pad = 0;
         // the step-2 pass with the first m rows of X as the batch
-        rc = run_kmv(c, c->X, c->d, c->norms.as<float>(), nullptr, m, c->X, c->d,
-                     c->norms.as<float>(), nullptr, c->n, c->alpha.as<float>(), &slices, &rows_pad,
-                     false, false);
+        auto pass = [&]() {
+            if (use_split_step(c, m)) return run_split_pass(c, nullptr, m, &slices, &rows_pad, false, false);
+            return run_kmv(c, c->X, c->d, c->norms.as<float>(), nullptr, m, c->X, c->d,
+                           c->norms.as<float>(), nullptr, c->n, c->alpha.as<float>(), &slices,
+                           &rows_pad, false, false);
+        };
+        if (use_split_step(c, m)) {
+            if (c->Qp.ensure(packed_bytes(c, m)) != hipSuccess)
+                rc = fail(EP_ENOMEM, "packed batch of %lld rows", (long long)m);
+            else
+                rc = pack_queries(c, c->X, nullptr, m, c->Qp.as<char>(), true);
+            if (rc) break;
+        }
+        rc = pass();
         if (rc) break;
         if (hipEventRecord(e0, c->stream) != hipSuccess) rc = fail(EP_EDEVICE, "event record");
-        for (int r = 0; r < reps && rc == EP_OK; ++r)
-            rc = run_kmv(c, c->X, c->d, c->norms.as<float>(), nullptr, m, c->X, c->d,
-                         c->norms.as<float>(), nullptr, c->n, c->alpha.as<float>(), &slices,
-                         &rows_pad, false, false);
+        for (int r = 0; r < reps && rc == EP_OK; ++r) rc = pass();
         float t = 0.f;
         if (rc == EP_OK && (hipEventRecord(e1, c->stream) != hipSuccess ||
                             hipEventSynchronize(e1) != hipSuccess ||

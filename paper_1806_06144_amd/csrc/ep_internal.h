@@ -111,6 +111,67 @@ struct KblockArgs {
 };
 hipError_t kblock_launch(const KblockArgs& a, hipStream_t s);
 
+// Split-precision fused pass (skmv.hip; operand layouts in split.h).
+// Packs rows into panels of P rows (two scaled fp16 planes, then P norms and
+// P inverse scales): rows idx[0 .. rows) of X, or rows 0 .. rows - 1.
+struct PackArgs {
+    const float* X;            // row-major, leading dimension d
+    int64_t n;                 // rows of X (bound of idx)
+    int64_t d;
+    const int64_t* idx;        // NULL: identity
+    int64_t rows;
+    const float* norms_in;     // per row of X: |x|^2 and inverse scale, or
+    const float* inv_in;       //   both NULL (computed)
+    char* out;                 // round_up(rows, P) / P panels
+    int64_t P;
+    float* norms_out;          // per packed row (may be NULL)
+    float* inv_out;
+    int* err;                  // set where idx is out of range
+    bool queries;              // planes of feature steps [neg0, neg1) negated
+    int64_t nk, panel;         // (set by the launch)
+    int neg0, neg1;
+};
+// Feature steps [neg0, neg1) over which the fused pass accumulates the
+// negated dot product (-1, -1: none). An MFMA drops the addends' bits below
+// the accumulator's last places towards minus infinity; turning the sign
+// for part of the sum makes the shifts cancel.
+void sign_steps(int64_t nk, int* neg0, int* neg1);
+hipError_t launch_pack_rows(PackArgs a, hipStream_t s);
+// Planes (split.h) of rows x l weights with leading dimension ldw.
+hipError_t launch_pack_weights(const float* W, int64_t rows, int64_t l, int64_t ldw, int64_t lt,
+                               void* planes, hipStream_t s);
+
+struct SplitArgs {
+    const char* Q;             // packed queries, panels of kQPanel rows
+    int64_t q_panel;           // bytes of a panel
+    const int64_t* qid;        // global row id of each query (NULL: none)
+    int64_t nq;
+    const char* C;             // packed centres, panels of kCPanel rows
+    int64_t c_panel;
+    int64_t nc;
+    int64_t nk;                // 32-feature steps
+    int neg0, neg1;            // (sign_steps, set by the launch)
+    const char* W;             // weight planes, lt label tiles of 16
+    int lt;
+    float* out;                // partials [splits][out_rows][ldw]
+    int64_t out_rows;
+    int64_t ldw;
+    int64_t tps;               // centre panels per split
+    int kind;
+    float scale;
+    const int* kpos;           // as in KmvArgs
+    float* ksb;
+    int64_t ldk;
+};
+struct SplitPlan {
+    int splits;
+    int64_t tps;               // centre panels per split
+    double cost;               // predicted time, in panels of one workgroup
+};
+constexpr int kMaxFusedTiles = 10;   // label tiles whose accumulators fit the fused pass
+SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, int max_slices);
+hipError_t split_launch(SplitArgs a, const SplitPlan& p, hipStream_t s);
+
 // Thin products of steps 4-5 (thin_gemm.hip):
 //   C[p] = sum over depth chunk p of A(i, kk) B(kk, j), i < M, j < N,
 // B row-major (K x N, ldb); A row-major (M x K, lda) or, with a_t, the
@@ -134,6 +195,8 @@ struct ThinGemmArgs {
     const int64_t* r;
     float coef;
     int64_t N_valid;
+    unsigned short* planes;    // split planes of alpha (NULL: none), lt label tiles
+    int64_t lt;
 };
 struct ThinGemmPlan {
     int64_t kc = 0;        // depth per chunk, a multiple of the 64-deep accumulation block
@@ -158,11 +221,13 @@ hipError_t launch_gather_rows(const float* X, int64_t n, int64_t d, const float*
                               const int64_t* idx, int64_t m, int64_t m_pad,
                               float* out, float* out_norms, int* err, hipStream_t s);
 // R gets r_rows rows (zero beyond m) so that it can serve as the weights of
-// a fused pass whose centres are the batch rows.
+// a fused pass whose centres are the batch rows. `planes` (may be NULL): the
+// split planes of alpha, updated with it (lt label tiles).
 hipError_t launch_reduce_residual(const float* part, int slices, int64_t rows_pad,
                                   int64_t ldw, int64_t m, int64_t l, const float* y,
                                   float* f_out, float* R, int64_t r_rows, float* alpha,
-                                  int64_t n, const int64_t* t, float coef, hipStream_t s);
+                                  int64_t n, const int64_t* t, float coef,
+                                  unsigned short* planes, int64_t lt, hipStream_t s);
 hipError_t launch_reduce_rows(const float* part, int slices, int64_t rows_pad,
                               int64_t ldw, int64_t rows, int64_t cols, float* out,
                               int64_t ldo, hipStream_t s);

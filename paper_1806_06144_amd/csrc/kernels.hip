@@ -3,6 +3,7 @@
 // batch-block update (Algorithm 1 step 3), and the float64 subsample kernel
 // matrix of the initialisation.
 #include "ep_internal.h"
+#include "split.h"
 
 #include <math.h>
 
@@ -57,7 +58,7 @@ __global__ void __launch_bounds__(256) gather_rows_kernel(const float* X, int64_
 __global__ void __launch_bounds__(256) reduce_residual_kernel(
     const float* part, int slices, int64_t rows_pad, int64_t ldw, int64_t m, int64_t l,
     const float* y, float* f_out, float* R, int64_t r_rows, float* alpha, int64_t n,
-    const int64_t* t, float coef) {
+    const int64_t* t, float coef, unsigned short* planes, int64_t lt) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= r_rows * ldw) return;
     const int64_t b = e / ldw;
@@ -72,7 +73,11 @@ __global__ void __launch_bounds__(256) reduce_residual_kernel(
     if (f_out) f_out[b * l + c] = f;
     R[e] = r;
     const int64_t row = t[b];
-    if (row >= 0 && row < n) alpha[row * ldw + c] -= coef * r;
+    if (row >= 0 && row < n) {
+        const float a = alpha[row * ldw + c] - coef * r;
+        alpha[row * ldw + c] = a;
+        if (planes) store_weight(planes, weight_elem(row, c, lt), a);
+    }
 }
 
 __global__ void __launch_bounds__(256) reduce_rows_kernel(const float* part, int slices,
@@ -183,9 +188,11 @@ hipError_t launch_gather_rows(const float* X, int64_t n, int64_t d, const float*
 hipError_t launch_reduce_residual(const float* part, int slices, int64_t rows_pad, int64_t ldw,
                                   int64_t m, int64_t l, const float* y, float* f_out, float* R,
                                   int64_t r_rows, float* alpha, int64_t n, const int64_t* t,
-                                  float coef, hipStream_t s) {
+                                  float coef, unsigned short* planes, int64_t lt,
+                                  hipStream_t s) {
     hipLaunchKernelGGL(reduce_residual_kernel, dim3(blocks_for(r_rows * ldw)), dim3(256), 0, s,
-                       part, slices, rows_pad, ldw, m, l, y, f_out, R, r_rows, alpha, n, t, coef);
+                       part, slices, rows_pad, ldw, m, l, y, f_out, R, r_rows, alpha, n, t, coef,
+                       planes, lt);
     return hipGetLastError();
 }
 

@@ -1,0 +1,549 @@
+// Fused kernel-block contraction on the 16-bit matrix cores of gfx950:
+//
+//   out[q, :] = sum_j k(q, c_j) W[j, :]      (Algorithm 1 step 2, prediction)
+//
+// the same pass as kmv.hip, with both float32 products replaced by sums of
+// 16-bit products that lose nothing against float32 (split.h): distances as
+// three fp16 products of two planes, the contraction with the weights as six
+// bf16 products of three planes, all accumulated in float32. The fp16 / bf16
+// MFMA runs 16 times as many products per cycle as the fp32 one, so the
+// distance product costs 3/16 and the contraction 6/16 of what it did.
+//
+// Bound by the 16-bit MFMA rate under this card's power limit (a large
+// library product reaches 1.14 to 1.36 of the nominal 2.5 PFLOP/s). Of it
+// the pass reaches, counting its three and six products: 1.0 PFLOP/s at
+// 60000 x 784, 10 labels, 1310 queries (382 us; the float32 pass 1070 us),
+// 1.25 at 50000 x 3072 with 10000 queries, 0.92 at 1.1 M x 440, 144 labels,
+// 1257 queries (6.55 ms; float32 12.9 ms).
+//
+// Four waves share a panel of 128 centres through LDS (direct-to-LDS loads
+// of 32 features, three stages ahead in four slots, one barrier per stage);
+// each wave owns 64 queries (32 beyond 16 labels), whose operands it reads
+// from the L2 one stage ahead. Kernel values never leave the registers: the
+// accumulators of the distance product are the operands of the contraction
+// (weight_elem in split.h orders the weights to match). Two workgroups fit a
+// CU, so one's epilogue runs beside the other's products; a version with
+// twice the queries per wave and one workgroup per CU took 7.8 ms instead of
+// 6.6 at 144 labels.
+#include "ep_device.h"
+#include "ep_internal.h"
+#include "split.h"
+
+#include <algorithm>
+#include <cstdlib>
+#include <type_traits>
+
+namespace ep {
+
+namespace {
+
+constexpr int kSThreads = 256;                       // 4 waves
+constexpr int kSlotQuads = kCPanel / 16 * 2 * 64;    // 16-byte quads of one 32-feature stage
+
+// ---- packing ---------------------------------------------------------------
+
+// Packs 16 rows per workgroup: norms (float64 sums, as row_norms_kernel) and
+// row maxima first unless they are given, then the two scaled fp16 planes.
+// Rows past `rows` and gathered rows out of [0, n) are zero (norm 0, scale 1).
+template <bool VEC>
+__global__ void __launch_bounds__(256) pack_rows_kernel(PackArgs p) {
+    __shared__ float s_norm[16], s_inv[16], s_scale[16];
+    __shared__ int64_t s_row[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t tile = blockIdx.x;
+    if (tid < 16) {
+        const int64_t b = tile * 16 + tid;
+        int64_t src = b < p.rows ? b : -1;
+        if (p.idx && src >= 0) {
+            src = p.idx[b];
+            if (src < 0 || src >= p.n) {
+                atomicOr(p.err, 1);
+                src = -1;
+            }
+        }
+        s_row[tid] = src;
+        if (p.norms_in) {
+            s_norm[tid] = src >= 0 ? p.norms_in[src] : 0.f;
+            s_inv[tid] = src >= 0 ? p.inv_in[src] : 1.f;
+        }
+    }
+    __syncthreads();
+    if (!p.norms_in) {
+        for (int r = wave; r < 16; r += 4) {
+            const int64_t src = s_row[r];
+            double acc = 0.0;
+            float mx = 0.f;
+            if (src >= 0) {
+                const float* x = p.X + src * p.d;
+                for (int64_t j = lane; j < p.d; j += 64) {
+                    const float f = x[j];
+                    const double v = f;
+                    acc += v * v;
+                    mx = fmaxf(mx, fabsf(f));
+                }
+            }
+            for (int off = 32; off > 0; off >>= 1) {
+                acc += __shfl_down(acc, off, 64);
+                mx = fmaxf(mx, __shfl_down(mx, off, 64));
+            }
+            if (lane == 0) {
+                // largest element into [2^14, 2^15); exponents below -63
+                // (squares below the float32 range) share one scale
+                const int e = mx == 0.f ? 14
+                                        : min(127, max(-63, (int)(__builtin_bit_cast(unsigned, mx) >> 23) - 127));
+                s_norm[r] = (float)acc;
+                s_inv[r] = __builtin_bit_cast(float, (unsigned)(e - 14 + 127) << 23);
+            }
+        }
+        __syncthreads();
+    }
+    if (tid < 16) {
+        // a power of two: its reciprocal is exact
+        s_scale[tid] = 1.f / s_inv[tid];
+        const int64_t b = tile * 16 + tid;
+        const int64_t panel = b / p.P, at = b % p.P;
+        float* meta = reinterpret_cast<float*>(p.out + panel * p.panel + p.nk * (p.P / 16) * 2 * kFragBytes);
+        meta[at] = s_norm[tid];
+        meta[p.P + at] = s_inv[tid];
+        if (b < p.rows) {
+            if (p.norms_out) p.norms_out[b] = s_norm[tid];
+            if (p.inv_out) p.inv_out[b] = s_inv[tid];
+        }
+    }
+    __syncthreads();
+    const int row = lane & 15, g = lane >> 4;
+    const int64_t src = s_row[row];
+    const float sc = s_scale[row];
+    const float* x = p.X + (src >= 0 ? src : 0) * p.d;
+    const int64_t t_panel = p.P / 16;
+    char* out = p.out + (tile / t_panel) * p.panel + (tile % t_panel) * 2 * kFragBytes + lane * 16;
+    for (int64_t ks = wave; ks < p.nk; ks += 4) {
+        const int64_t c0 = ks * 32 + 8 * g;
+        const float sck = ks >= p.neg0 && ks < p.neg1 ? -sc : sc;
+        float v[8];
+        if (VEC) {
+            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 a = src >= 0 && c0 < p.d ? *reinterpret_cast<const float4*>(x + c0) : z;
+            const float4 b = src >= 0 && c0 + 4 < p.d ? *reinterpret_cast<const float4*>(x + c0 + 4) : z;
+            v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+            v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = src >= 0 && c0 + j < p.d ? x[c0 + j] : 0.f;
+        }
+        half8 hi, lo;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float s = v[j] * sck;
+            const _Float16 h = (_Float16)s;
+            hi[j] = h;
+            lo[j] = __builtin_isfinite(s) ? (_Float16)(s - (float)h) : (_Float16)0.f;
+        }
+        char* o = out + ks * t_panel * 2 * kFragBytes;
+        *reinterpret_cast<half8*>(o) = hi;
+        *reinterpret_cast<half8*>(o + kFragBytes) = lo;
+    }
+}
+
+// Planes of a whole weight matrix (rows x l floats, leading dimension ldw).
+__global__ void __launch_bounds__(256) pack_weights_kernel(const float* W, int64_t rows, int64_t l,
+                                                           int64_t ldw, int64_t lt,
+                                                           unsigned short* planes) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= rows * l) return;
+    const int64_t c = e / l, j = e - c * l;
+    store_weight(planes, weight_elem(c, j, lt), W[c * ldw + j]);
+}
+
+// ---- the fused pass --------------------------------------------------------
+
+// One workgroup = 4 waves owns 64 QB queries (QB blocks of 16 per wave) and a
+// contiguous range of centre panels of 128 rows, walked panel by panel.
+template <int KIND, int LT, int QB>
+__global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
+    constexpr int kWQ = 16 * QB;                     // queries per wave
+    constexpr int kSQ = 4 * kWQ;
+    __shared__ uintx4 xs0[kSlotQuads];
+    __shared__ uintx4 xs1[kSlotQuads];
+    __shared__ uintx4 xs2[kSlotQuads];
+    __shared__ uintx4 xs3[kSlotQuads];
+    __shared__ __attribute__((aligned(16))) float s_meta[2 * kCPanel];   // norms, inverse scales
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, g = lane >> 4;
+    const int tq = (int)((p.nq + kSQ - 1) / kSQ);
+    const int split = (int)blockIdx.x / tq;
+    const int qtile = (int)blockIdx.x - split * tq;
+    const int ntile = (int)((p.nc + kCPanel - 1) / kCPanel);
+    const int t0 = (int)min((int64_t)ntile, split * p.tps);
+    const int t1 = (int)min((int64_t)ntile, t0 + p.tps);
+    const int nk = (int)p.nk;
+
+    // this wave's queries, inside one packed panel (a wave past the last
+    // query only helps to move the centres)
+    const int64_t row0 = min((int64_t)qtile * kSQ + wave * kWQ,
+                             (p.nq + kQPanel - 1) / kQPanel * kQPanel - kWQ);
+    const bool live = (int64_t)qtile * kSQ + wave * kWQ < p.nq;
+    const char* qbase = p.Q + row0 / kQPanel * p.q_panel;
+    const int qb0 = (int)(row0 % kQPanel) / 16;
+    const __amdgpu_buffer_rsrc_t qrs = make_rsrc(reinterpret_cast<const float*>(qbase), p.q_panel);
+    const float* qmeta = reinterpret_cast<const float*>(qbase + (int64_t)nk * (kQPanel / 16) * 2 * kFragBytes);
+    float qn[QB], iq2[QB];
+    int qid[QB];
+#pragma unroll
+    for (int b = 0; b < QB; ++b) {
+        const int q = 16 * (qb0 + b) + col;
+        qn[b] = qmeta[q];
+        iq2[b] = -2.f * qmeta[kQPanel + q];
+        const int64_t row = row0 + 16 * b + col;
+        qid[b] = p.qid && row < p.nq ? (int)p.qid[row] : -1;
+    }
+
+    auto slot_of = [&](auto tag) -> uintx4* {
+        constexpr int S = decltype(tag)::value & 3;
+        if constexpr (S == 0) return xs0;
+        else if constexpr (S == 1) return xs1;
+        else if constexpr (S == 2) return xs2;
+        else return xs3;
+    };
+    auto panel_rsrc = [&](int t) {
+        return make_rsrc(reinterpret_cast<const float*>(p.C + t * p.c_panel), p.c_panel);
+    };
+    // stage ks of a centre panel, 16 contiguous kilobytes, straight into LDS
+    auto dma = [&](auto tag, __amdgpu_buffer_rsrc_t crs, int ks) {
+        uintx4* base = slot_of(tag);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int f = 4 * wave + i;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(crs, (lds_void*)(base + f * 64), 16, lane * 16,
+                                                     (ks * 16 + f) * kFragBytes, 0, 0);
+        }
+    };
+    uintx4 bq[2][QB][2];
+    auto qload = [&](uintx4 (&b)[QB][2], int ks) {
+#pragma unroll
+        for (int i = 0; i < QB; ++i)
+#pragma unroll
+            for (int pl = 0; pl < 2; ++pl)
+                b[i][pl] = __builtin_bit_cast(
+                    uintx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                qrs, lane * 16, (ks * 8 + (qb0 + i) * 2 + pl) * kFragBytes, 0));
+    };
+
+    floatx4 sacc[8][QB];
+    floatx4 oacc[LT][QB];
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+#pragma unroll
+        for (int b = 0; b < QB; ++b) sacc[c][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < LT; ++c)
+#pragma unroll
+        for (int b = 0; b < QB; ++b) oacc[c][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    auto step = [&](auto tag, __amdgpu_buffer_rsrc_t crs, int ks) {
+        constexpr int S = decltype(tag)::value;
+        // the queries' planes change sign here (sign_steps)
+        if (ks == p.neg0 || ks == p.neg1) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+#pragma unroll
+                for (int i = 0; i < QB; ++i) sacc[c][i] = -sacc[c][i];
+        }
+        if (ks + 1 < nk) qload(bq[(S & 1) ^ 1], ks + 1);
+        if (ks + 3 < nk) dma(std::integral_constant<int, (S + 3) & 3>{}, crs, ks + 3);
+        const uintx4* xs = slot_of(tag);
+        const uintx4 (&b)[QB][2] = bq[S & 1];
+        uintx4 a[2][2];
+        a[0][0] = xs[lane];
+        a[0][1] = xs[64 + lane];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            if (c < 7) {
+                a[(c + 1) & 1][0] = xs[(2 * c + 2) * 64 + lane];
+                a[(c + 1) & 1][1] = xs[(2 * c + 3) * 64 + lane];
+            }
+            const uintx4 ah = a[c & 1][0], al = a[c & 1][1];
+#pragma unroll
+            for (int i = 0; i < QB; ++i) sacc[c][i] = mfma_f16(al, b[i][0], sacc[c][i]);
+#pragma unroll
+            for (int i = 0; i < QB; ++i) sacc[c][i] = mfma_f16(ah, b[i][1], sacc[c][i]);
+#pragma unroll
+            for (int i = 0; i < QB; ++i) sacc[c][i] = mfma_f16(ah, b[i][0], sacc[c][i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wg_barrier<-1>();
+    };
+
+    auto value = [&](float s, float cn, float ci, int b) {
+        return kernel_value<KIND>(fmaf(s * ci, iq2[b], qn[b] + cn), p.scale);
+    };
+
+    auto prefetch = [&](int t) {
+        const __amdgpu_buffer_rsrc_t crs = panel_rsrc(t);
+        dma(std::integral_constant<int, 0>{}, crs, 0);
+        if (nk > 1) dma(std::integral_constant<int, 1>{}, crs, 1);
+        if (nk > 2) dma(std::integral_constant<int, 2>{}, crs, 2);
+        qload(bq[0], 0);
+    };
+    float4 meta = make_float4(0.f, 0.f, 0.f, 0.f);
+    int kp[2] = {-1, -1};
+    auto load_meta = [&](int t) {
+        if (wave == 0)
+            meta = *reinterpret_cast<const float4*>(p.C + t * p.c_panel +
+                                                    (int64_t)nk * 16 * kFragBytes + lane * 16);
+        if (p.kpos) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int64_t c = (int64_t)t * kCPanel + 64 * h + lane;
+                kp[h] = c < p.nc ? p.kpos[c] : -1;
+            }
+        }
+    };
+
+    if (t0 < t1) prefetch(t0);
+    for (int t = t0; t < t1; ++t) {
+        load_meta(t);
+        // stages 0..2 are in LDS for everyone; every wave has left the
+        // previous tile's epilogue
+        wg_barrier<0>();
+        if (wave == 0) reinterpret_cast<float4*>(s_meta)[lane] = meta;
+        const __amdgpu_buffer_rsrc_t crs = panel_rsrc(t);
+        for (int k0 = 0; k0 < nk; k0 += 4) {
+            step(std::integral_constant<int, 0>{}, crs, k0);
+            if (k0 + 1 < nk) step(std::integral_constant<int, 1>{}, crs, k0 + 1);
+            if (k0 + 2 < nk) step(std::integral_constant<int, 2>{}, crs, k0 + 2);
+            if (k0 + 3 < nk) step(std::integral_constant<int, 3>{}, crs, k0 + 3);
+        }
+        if (t + 1 < t1) prefetch(t + 1);
+        if (!live) continue;
+
+        // A query's own centre: its distance becomes minus infinity, which
+        // the clamp turns into 0 and the kernel value into 1 exactly.
+        {
+            int rel[QB];
+            bool any = false;
+#pragma unroll
+            for (int b = 0; b < QB; ++b) {
+                const int r = qid[b] - t * kCPanel;
+                const bool in = qid[b] >= 0 && r >= 0 && r < kCPanel && ((r >> 2) & 3) == g;
+                rel[b] = in ? 4 * (r >> 4) + (r & 3) : -1;
+                any |= in;
+            }
+            if (__any(any)) {
+#pragma unroll
+                for (int b = 0; b < QB; ++b)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (rel[b] == 4 * c + i) sacc[c][b][i] = __builtin_inff();
+            }
+        }
+        // Subsample centres: their kernel values also go to row kpos of ksb.
+        if (p.kpos) {
+            const uint64_t f0 = __ballot(kp[0] >= 0), f1 = __ballot(kp[1] >= 0);
+            if (f0 | f1) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const unsigned m16 = (unsigned)((c < 4 ? f0 : f1) >> (16 * (c & 3))) & 0xffffu;
+                    if (!m16) continue;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (!(m16 & (0x1111u << i))) continue;
+                        const int at = 16 * c + 4 * g + i;
+                        const int pos = __shfl(kp[c >> 2], at & 63, 64);
+                        const float cn = s_meta[at], ci = s_meta[kCPanel + at];
+                        if (pos >= 0) {
+                            float* o = p.ksb + pos * p.ldk + row0 + col;
+#pragma unroll
+                            for (int b = 0; b < QB; ++b) o[16 * b] = value(sacc[c][b][i], cn, ci, b);
+                        }
+                    }
+                }
+            }
+        }
+        const __amdgpu_buffer_rsrc_t wrs =
+            make_rsrc(reinterpret_cast<const float*>(p.W + (int64_t)t * 4 * LT * 3 * kFragBytes),
+                      (int64_t)4 * LT * 3 * kFragBytes);
+        // (the scheduling barriers keep the compiler from lengthening the
+        // weights' lifetimes until they no longer fit the registers)
+        auto load_w = [&](uintx4 (&w)[3], int f) {
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                w[pl] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                       wrs, lane * 16, (f * 3 + pl) * kFragBytes, 0));
+        };
+        uintx4 wf[2][3];
+        load_w(wf[0], 0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            uintx4 kf[QB][3];
+            const floatx4 cn0 = *reinterpret_cast<const floatx4*>(&s_meta[32 * u + 4 * g]);
+            const floatx4 cn1 = *reinterpret_cast<const floatx4*>(&s_meta[32 * u + 16 + 4 * g]);
+            const floatx4 ci0 = *reinterpret_cast<const floatx4*>(&s_meta[kCPanel + 32 * u + 4 * g]);
+            const floatx4 ci1 = *reinterpret_cast<const floatx4*>(&s_meta[kCPanel + 32 * u + 16 + 4 * g]);
+#pragma unroll
+            for (int b = 0; b < QB; ++b) {
+                float kv[8];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    kv[i] = value(sacc[2 * u][b][i], cn0[i], ci0[i], b);
+                    kv[4 + i] = value(sacc[2 * u + 1][b][i], cn1[i], ci1[i], b);
+                    if (u & 1) {                     // see the contraction below
+                        kv[i] = -kv[i];
+                        kv[4 + i] = -kv[4 + i];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    unsigned h, m, l;
+                    split3(kv[2 * i], kv[2 * i + 1], h, m, l);
+                    kf[b][0][i] = h;
+                    kf[b][1][i] = m;
+                    kf[b][2][i] = l;
+                }
+                sacc[2 * u][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+                sacc[2 * u + 1][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < LT; ++j) {
+                const int f = u * LT + j;
+                if (f + 1 < 4 * LT) load_w(wf[(f + 1) & 1], f + 1);
+                const uintx4 (&w)[3] = wf[f & 1];
+                // The products of 32 centres are summed from zero, smallest
+                // first, and added to the running sum outside the MFMA, every
+                // other time with both signs turned: an MFMA drops the
+                // addends' bits below the accumulator's last places towards
+                // minus infinity, which over the thousands of steps of a
+                // split shifts every sum the same way (7e-6 of the result at
+                // 1.1 million centres in one chain, 1e-6 from zero each time).
+                constexpr int wp[6] = {2, 0, 1, 1, 0, 0}, kq[6] = {0, 2, 1, 0, 1, 0};
+                floatx4 t[QB];
+#pragma unroll
+                for (int b = 0; b < QB; ++b) t[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int x = 0; x < 6; ++x)
+#pragma unroll
+                    for (int b = 0; b < QB; ++b) t[b] = mfma_bf16(w[wp[x]], kf[b][kq[x]], t[b]);
+#pragma unroll
+                for (int b = 0; b < QB; ++b) oacc[j][b] += u & 1 ? -t[b] : t[b];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    if (!live) return;
+    // element i of tile j, block b: label 16 j + 4 g + i, query 16 b + col
+    float* o = p.out + ((int64_t)split * p.out_rows + row0) * p.ldw + 4 * g;
+#pragma unroll
+    for (int b = 0; b < QB; ++b)
+#pragma unroll
+        for (int j = 0; j < LT; ++j)
+            *reinterpret_cast<floatx4*>(o + (int64_t)(16 * b + col) * p.ldw + 16 * j) = oacc[j][b];
+}
+
+typedef void (*SplitFn)(SplitArgs);
+
+template <int KIND>
+SplitFn fused_fn(int lt) {                          // (query blocks: split_rows)
+    switch (lt) {
+        case 1: return skmv_kernel<KIND, 1, 4>;
+        case 2: return skmv_kernel<KIND, 2, 2>;
+        case 3: return skmv_kernel<KIND, 3, 2>;
+        case 4: return skmv_kernel<KIND, 4, 2>;
+        case 5: return skmv_kernel<KIND, 5, 2>;
+        case 6: return skmv_kernel<KIND, 6, 2>;
+        case 7: return skmv_kernel<KIND, 7, 2>;
+        case 8: return skmv_kernel<KIND, 8, 2>;
+        case 9: return skmv_kernel<KIND, 9, 2>;
+        default: return skmv_kernel<KIND, 10, 2>;
+    }
+}
+
+// Queries per workgroup of the fused pass with lt label tiles.
+int split_rows(int64_t lt) { return lt <= 1 ? 256 : 128; }
+
+int split_slots(SplitFn fn) {
+    int dev = 0, cus = 256, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        cus = 256;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, kSThreads, 0) != hipSuccess || per < 1)
+        per = 1;
+    return per * cus;
+}
+
+}  // namespace
+
+void sign_steps(int64_t nk, int* neg0, int* neg1) {
+    *neg0 = *neg1 = -1;
+    if (nk < 4) return;
+    // the shift grows with the sum: a quarter of the steps, then half with
+    // the other sign, then a quarter cancel for a sum growing evenly
+    int64_t best = nk * nk;
+    for (int64_t a = nk / 4; a <= nk / 4 + 1; ++a)
+        for (int64_t b = nk - nk / 4 - 1; b <= nk - nk / 4; ++b) {
+            const int64_t off = std::abs(a * a - (b * b - a * a) + (nk * nk - b * b));
+            if (a < b && off < best) {
+                best = off;
+                *neg0 = (int)a;
+                *neg1 = (int)b;
+            }
+        }
+}
+
+hipError_t launch_pack_rows(PackArgs a, hipStream_t s) {
+    if (a.rows <= 0) return hipSuccess;
+    a.nk = feature_steps(a.d);
+    a.neg0 = a.neg1 = -1;
+    if (a.queries) sign_steps(a.nk, &a.neg0, &a.neg1);
+    a.panel = panel_bytes(a.P, a.d);
+    const unsigned grid = (unsigned)(round_up(a.rows, a.P) / 16);
+    const bool vec = a.d % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0;
+    if (vec) hipLaunchKernelGGL(pack_rows_kernel<true>, dim3(grid), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(pack_rows_kernel<false>, dim3(grid), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_weights(const float* W, int64_t rows, int64_t l, int64_t ldw, int64_t lt,
+                               void* planes, hipStream_t s) {
+    if (rows <= 0) return hipSuccess;
+    hipLaunchKernelGGL(pack_weights_kernel, dim3((unsigned)ceil_div(rows * l, 256)), dim3(256), 0, s,
+                       W, rows, l, ldw, lt, static_cast<unsigned short*>(planes));
+    return hipGetLastError();
+}
+
+SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, int max_slices) {
+    const SplitFn fn = kind == 0 ? fused_fn<0>((int)lt) : fused_fn<1>((int)lt);
+    const int64_t slots = split_slots(fn);
+    const int64_t tq = ceil_div(std::max<int64_t>(nq, 1), split_rows(lt));
+    const int64_t nt = ceil_div(std::max<int64_t>(nc, 1), kCPanel);
+    SplitPlan best{1, nt, 0.0};
+    double bt = 1e300;
+    for (int64_t P = 1; P <= nt && P <= max_slices; ++P) {
+        const int64_t per = ceil_div(nt, P);
+        if (ceil_div(nt, per) != P) continue;
+        const double t = (double)ceil_div(tq * P, slots) * ((double)per + 0.5);
+        if (t < bt) {
+            bt = t;
+            best.splits = (int)P;
+            best.tps = per;
+            best.cost = t;
+        }
+    }
+    return best;
+}
+
+hipError_t split_launch(SplitArgs a, const SplitPlan& p, hipStream_t s) {
+    a.tps = p.tps;
+    sign_steps(a.nk, &a.neg0, &a.neg1);
+    const SplitFn fn = a.kind == 0 ? fused_fn<0>(a.lt) : fused_fn<1>(a.lt);
+    const int64_t tq = ceil_div(std::max<int64_t>(a.nq, 1), split_rows(a.lt));
+    hipLaunchKernelGGL(fn, dim3((unsigned)(tq * p.splits)), dim3(kSThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace ep

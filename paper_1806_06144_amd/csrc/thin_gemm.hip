@@ -32,6 +32,7 @@
 // element).
 #include "ep_device.h"
 #include "ep_internal.h"
+#include "split.h"
 
 namespace ep {
 
@@ -155,7 +156,12 @@ __global__ void __launch_bounds__(kGThreads) thin_gemm_kernel(ThinGemmArgs p) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int64_t row = i0 + wm * 32 + acc_row(v, lane);
-            if (row < p.M) p.alpha[p.r[row] * p.ldalpha + col] += p.coef * sum[v];
+            if (row < p.M) {
+                const int64_t r = p.r[row];
+                const float a = p.alpha[r * p.ldalpha + col] + p.coef * sum[v];
+                p.alpha[r * p.ldalpha + col] = a;
+                if (p.planes) store_weight(p.planes, weight_elem(r, col, p.lt), a);
+            }
         }
     } else {
         if (col >= p.N) return;

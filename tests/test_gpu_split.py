@@ -1,0 +1,107 @@
+"""The split-precision fused pass against float64, where its tiling, packing
+and scaling can go wrong: queries around the 16-, 64-, 128- and 256-row edges,
+centres around the 128-row panel, features around the 32-feature step and the
+points where the accumulated sign turns, label tiles of 16 full and one past,
+rows of very different scale, and rows that are not 16-byte aligned."""
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_common import Gpu, TOL_STEP, bw32, kernel_id, rel
+
+EPS = 2.0 ** -24
+
+
+def _bound(X, Z, a, kernel, bw):
+    """Elementwise bound of a float32 evaluation of K(Z, X) a: the squared
+    distance |x|^2 + |z|^2 - 2 x.z is off by at most a few roundings of its
+    terms (norms and dot product rounded, the dot product accumulated over
+    d / 32 instructions of three products each, its scaled operands good to
+    2^-22), the kernel value by that times its derivative (the Laplacian's
+    at the smallest distance the error allows) and a few roundings of exp2 /
+    sqrt, the sum over centres by its terms times the depth of a chain."""
+    d = X.shape[1]
+    xn, zn = (X.astype(np.float64) ** 2).sum(1), (Z.astype(np.float64) ** 2).sum(1)
+    d2 = np.maximum(zn[:, None] + xn[None] - 2.0 * Z.astype(np.float64) @ X.T.astype(np.float64), 0)
+    e2 = (6 + np.sqrt(d) / 4) * EPS * (zn[:, None] + xn[None])
+    if kernel == "gaussian":
+        K = np.exp(-d2 / (2 * bw * bw))
+        dK = K * (e2 / (2 * bw * bw) + 8 * EPS * (1 + d2 / (2 * bw * bw)))
+    else:
+        r = np.sqrt(d2)
+        K = np.exp(-r / bw)
+        dr = np.minimum(np.sqrt(e2), e2 / np.maximum(r, 1e-300))
+        dK = K * (np.expm1(dr / bw) + 8 * EPS * (1 + r / bw))
+    chain = (8 + np.sqrt(X.shape[0])) * EPS
+    return (dK + chain * K) @ np.abs(a.astype(np.float64)) + 1e-30
+
+
+# Passes of at most 2^27 multiply-adds (queries counted in tiles of 64) take
+# the float32 pass: n is large enough that these do not, and sits on, one
+# past or one short of a 128-row panel.
+CASES = [
+    # kernel, n, d, l, n_z
+    ("gaussian", 128 * 513, 32, 16, 64), ("laplacian", 128 * 250 + 1, 33, 17, 65),
+    ("gaussian", 128 * 530 - 1, 32, 1, 1), ("laplacian", 128 * 45, 95, 15, 256),
+    ("gaussian", 128 * 36 + 1, 97, 32, 257), ("gaussian", 128 * 65 + 1, 128, 33, 128),
+    ("laplacian", 128 * 64 - 1, 129, 48, 129), ("gaussian", 128 * 52, 160, 160, 127),
+    ("laplacian", 128 * 35 + 4, 161, 144, 130), ("gaussian", 128 * 16 + 2, 1030, 100, 63),
+    ("gaussian", 300000, 7, 3, 65), ("laplacian", 128 * 9 - 2, 416, 80, 300),
+    ("gaussian", 128 * 19 + 64, 224, 65, 250), ("laplacian", 128 * 2 + 1, 2500, 10, 320),
+    ("gaussian", 100, 8200, 20, 200),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kernel,n,d,l,n_z", CASES)
+@pytest.mark.parametrize("law", ["normal", "positive", "scales"])
+def test_predict_edges(kernel, n, d, l, n_z, law):
+    assert -(-n_z // 64) * 64 * n * d > 2 ** 27
+    rng = np.random.default_rng(n + d)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    Z = rng.standard_normal((n_z, d)).astype(np.float32)
+    if law == "positive":
+        X, Z = np.abs(X), np.abs(Z)
+    if law == "scales":          # rows from 2^-30 to 2^10, zero rows among them
+        X *= np.exp2(rng.integers(-30, 11, (n, 1))).astype(np.float32)
+        Z *= np.exp2(rng.integers(-30, 11, (n_z, 1))).astype(np.float32)
+        X[::17] = 0
+        Z[::13] = 0
+    Z[0] = X[n // 2]             # a repeated row
+    a = (rng.standard_normal((n, l)) * np.exp2(rng.integers(-20, 3, (n, 1)))).astype(np.float32)
+    bw = bw32(np.sqrt(d) * (0.8 if kernel == "gaussian" else 0.6))
+    with Gpu(X, l, kernel, bw, min(n, 20), 2, np.arange(min(n, 20))) as g:
+        g.set_alpha(a)
+        P = g.predict(Z)
+    P_o = oracle.predict(X.astype(np.float64), a.astype(np.float64), Z.astype(np.float64),
+                         kernel_id(kernel), bw)
+    b = _bound(X, Z, a, kernel, bw)
+    worst = np.max(np.abs(P - P_o) / b)
+    assert worst <= 1.0, worst
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m", [63, 64, 65, 128, 129, 255, 256, 257, 400])
+@pytest.mark.parametrize("d,l", [(699, 12), (700, 30)])
+def test_step_batch_edges(m, d, l):
+    """Own centres (k = 1), kept subsample columns and the planes of alpha
+    after each update, over two steps."""
+    n, s, k, bw = 3001, 150, 12, bw32(1.3)
+    rng = np.random.default_rng(m)
+    X = (rng.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    Y = np.eye(l, dtype=np.float32)[rng.integers(0, l, n)]
+    a0 = (rng.standard_normal((n, l)) / np.sqrt(n)).astype(np.float32)
+    r = rng.choice(n, s, replace=False)
+    st = oracle.setup(X, oracle.GAUSSIAN, bw, s, k, r)
+    assert -(-m // 64) * 64 * n * d > 2 ** 27
+    a_o = a0
+    with Gpu(X, l, "gaussian", bw, s, k, r) as g:
+        g.set_alpha(a0)
+        for _ in range(2):
+            t = rng.choice(n, m, replace=False)
+            F = g.step(t, Y[t])
+            a_n, F_o = oracle.step(st, a_o, t, Y[t])
+            assert rel(F, F_o) < TOL_STEP
+            a_o = a_n
+        assert rel(g.alpha() - a0, a_o - a0) < TOL_STEP
