@@ -224,23 +224,33 @@ unsigned short* planes_of(ep_ctx* c) {
 }
 
 // Whether F = K(Q, X) alpha takes the split-precision fused pass: where its
-// operands are held (setup_split), the blocked form is not asked for and
+// operands are held (setup_split), no other form is asked for (beyond
+// kMaxFusedTiles label tiles the split pass stores its kernel values) and
 // the pass has more than 2^27 multiply-adds (queries counted in tiles of 64).
 // Below that both passes are a few microseconds of work behind their
 // latency, and the float32 pass spreads it over four times as many
 // workgroups (n = 2000, d = 64, 256 queries: 16 against 19 us).
 bool use_split(const ep_ctx* c, int64_t nq) {
-    return c->split && c->contract != EP_CONTRACT_BLOCKED && c->lt16 <= kMaxFusedTiles &&
+    if (c->contract == EP_CONTRACT_BLOCKED ||
+        (c->contract == EP_CONTRACT_FUSED && c->lt16 > kMaxFusedTiles))
+        return false;
+    return c->split &&
            (double)round_up(nq, kBM) * (double)c->n * (double)c->d > (double)(1 << 27);
 }
-// The same for a training step. Laplacian steps on rows of more than 2048
-// features stay on the float32 pass: there a step's result depends on the
-// summation order at the 5e-5 level from the second step on (n = 50000,
-// d = 3072, uniform features: 5.3e-5 of float64 with the float32 pass, 4.1e-5
-// with this one, 6e-5 between the two), more than a change of kernel may
-// move it. It would take 2.4 ms instead of 7.5 ms there.
+// The same for a training step. Two ranges stay on the float32 pass, because
+// there a step's result depends on the summation order by more than a change
+// of kernel may move it (4e-5), from the second step of a run on:
+//  - Laplacian steps on rows of more than 2048 features (n = 50000, d = 3072,
+//    uniform features: 5.3e-5 off float64 with the float32 pass, 4.1e-5 with
+//    the split one, 6e-5 between the two; 7.5 against 2.4 ms);
+//  - more than 160 labels with batches of more than 2048 rows or more than
+//    2^29 kernel entries (n = 1.28 M, d = 2048, l = 1000, m = 3561: 7.1e-5,
+//    6.0e-5, 7.5e-5; 203 against 90 ms; n = 256316, m = 2964: 7.3e-5 between
+//    the two). At n = 160000, m = 1601 the two are 2.3e-5 apart.
 bool use_split_step(const ep_ctx* c, int64_t m) {
-    return use_split(c, m) && !(c->kind == EP_LAPLACIAN && c->d > 2048);
+    return use_split(c, m) && !(c->kind == EP_LAPLACIAN && c->d > 2048) &&
+           !(c->lt16 > kMaxFusedTiles &&
+             (m > 2048 || (double)m * (double)c->n > (double)(1 << 29)));
 }
 
 // Packs query rows for the split pass into `out`: rows idx[0 .. nq) of Z, or
@@ -270,9 +280,33 @@ size_t packed_bytes(const ep_ctx* c, int64_t nq) {
     return (size_t)ceil_div(nq, kQPanel) * panel_bytes(kQPanel, c->d);
 }
 
-// The split-precision fused pass over all centres for nq packed queries.
+constexpr size_t kValueBudget = size_t(4) << 30;    // bytes of stored kernel values
+
+// Bytes of the kernel values' planes of nq queries and nc centres.
+int64_t kvalue_bytes(int64_t nq, int64_t nc) {
+    return round_up(nq, kQPanel) * round_up(nc, kCPanel) * 6;
+}
+
+// The split pass over all centres for nq packed queries, with room for
+// `slices` partial sums in `part`. Up to kMaxFusedTiles label tiles one fused
+// launch; beyond that, chunk by chunk, the kernel values' planes of a chunk
+// of centres into kbuf (at least one panel of them) and their product with
+// the weights into the same partial sums.
+SplitPlan plan_split(const ep_ctx* c, int64_t nq, int64_t max_slices, size_t kbytes) {
+    const int ms = (int)std::min<int64_t>(256, max_slices);
+    if (c->lt16 <= kMaxFusedTiles) return split_plan(nq, c->n, c->lt16, c->kind, ms);
+    const int64_t panels = ceil_div(c->n, kCPanel);
+    const int64_t fit = (int64_t)(kbytes / kvalue_bytes(nq, kCPanel));
+    const int64_t chunks = ceil_div(panels, std::max<int64_t>(1, fit));
+    const int64_t per = ceil_div(panels, chunks);
+    SplitPlan pl = wmul_plan(nq, 4 * per, c->lt16, ms);
+    pl.chunk = per;
+    pl.cost *= (double)chunks;
+    return pl;
+}
+
 int run_split(ep_ctx* c, const char* Q, const int64_t* qid, int64_t nq, const SplitPlan& plan,
-              float* part, int64_t rows_pad, bool timed, bool capture) {
+              float* part, int64_t rows_pad, char* kbuf, bool timed, bool capture) {
     SplitArgs a{};
     a.Q = Q;
     a.q_panel = panel_bytes(kQPanel, c->d);
@@ -296,21 +330,63 @@ int run_split(ep_ctx* c, const char* Q, const int64_t* qid, int64_t nq, const Sp
     }
     int rc = EP_OK;
     if (timed && (rc = record(c->stream, c->kmv_ev, true))) return rc;
-    HIP_TRY(split_launch(a, plan, c->stream));
+    if (c->lt16 <= kMaxFusedTiles) {
+        HIP_TRY(split_launch(a, plan, c->stream));
+    } else {
+        const int64_t panels = ceil_div(c->n, kCPanel);
+        a.lt = 0;
+        a.kplanes = kbuf;
+        a.kgroups = 4 * plan.chunk;
+        for (int64_t p0 = 0; p0 < panels; p0 += plan.chunk) {
+            const int64_t np = std::min(plan.chunk, panels - p0);
+            a.c_base = p0 * kCPanel;
+            a.C = c->Xp.as<char>() + p0 * a.c_panel;
+            a.nc = std::min(np * kCPanel, c->n - a.c_base);
+            if (capture) a.kpos = c->kpos.as<int>() + a.c_base;
+            HIP_TRY(split_launch(a, split_plan(nq, a.nc, 0, c->kind, 1 << 20), c->stream));
+            WmulArgs w{};
+            w.K = kbuf;
+            w.kgroups = a.kgroups;
+            w.nq = nq;
+            w.lt = (int)c->lt16;
+            w.W = c->wplanes.as<char>() + p0 * 4 * c->lt16 * 3 * kFragBytes;
+            w.groups = (int)(4 * np);
+            w.out = part;
+            w.out_rows = rows_pad;
+            w.ldw = c->l_pad;
+            w.accumulate = p0 > 0;
+            SplitPlan wp = plan;
+            wp.tps = 4 * ceil_div(np, plan.splits);
+            HIP_TRY(wmul_launch(w, wp, c->stream));
+        }
+    }
     if (timed && (rc = record(c->stream, c->kmv_ev, false))) return rc;
     return EP_OK;
 }
 
-// The same with the context's own partial sums.
+// The same with the context's own buffers.
 int run_split_pass(ep_ctx* c, const int64_t* qid, int64_t nq, int* slices, int64_t* rows_pad,
                    bool timed, bool capture) {
     *rows_pad = round_up(std::max<int64_t>(nq, 1), kBM);
-    const SplitPlan plan =
-        split_plan(nq, c->n, c->lt16, c->kind, max_slices_for(*rows_pad, c->l_pad));
+    size_t kbytes = 0;
+    if (c->lt16 > kMaxFusedTiles) {
+        // one chunk's kernel values: at most 4 GiB, less where that does
+        // not fit (a chunk is as good as its launches are full)
+        kbytes = std::min((size_t)kvalue_bytes(nq, c->n), kValueBudget);
+        const size_t least = (size_t)kvalue_bytes(nq, kCPanel);
+        hipError_t e = c->kbuf.ensure(std::max(kbytes, least));
+        while (e == hipErrorOutOfMemory && kbytes > least) {
+            (void)hipGetLastError();
+            kbytes /= 2;
+            e = c->kbuf.ensure(std::max(kbytes, least));
+        }
+        HIP_TRY(e);
+    }
+    const SplitPlan plan = plan_split(c, nq, max_slices_for(*rows_pad, c->l_pad), kbytes);
     *slices = plan.splits;
     HIP_TRY(c->part.ensure((size_t)plan.splits * (size_t)(*rows_pad) * c->l_pad * sizeof(float)));
-    return run_split(c, c->Qp.as<char>(), qid, nq, plan, c->part.as<float>(), *rows_pad, timed,
-                     capture);
+    return run_split(c, c->Qp.as<char>(), qid, nq, plan, c->part.as<float>(), *rows_pad,
+                     c->kbuf.as<char>(), timed, capture);
 }
 
 constexpr size_t kKBlockBudget = size_t(2) << 30;   // bytes of one chunk's kernel block
@@ -650,7 +726,7 @@ int setup_split(ep_ctx* c) {
     const size_t wp = (size_t)weight_plane_bytes(c->n_pad, c->lt16);
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-    c->split = n < (int64_t(1) << 31) - kCPanel && lt <= kMaxFusedTiles && xp + wp <= free_b / 2;
+    c->split = n < (int64_t(1) << 31) - kCPanel && lt < (1 << 20) && xp + wp <= free_b / 2;
     if (c->split && (c->Xp.ensure(xp) != hipSuccess || c->wplanes.ensure(wp) != hipSuccess ||
                      c->xinv.ensure((size_t)n * sizeof(float)) != hipSuccess)) {
         (void)hipGetLastError();       // another allocation took the memory meanwhile
@@ -1082,22 +1158,25 @@ int ep_predict_noalloc(ep_ctx* c, const float* Z, int64_t n_z, float* out) {
                     "ep_predict_noalloc: %lld label columns exceed the %zu-float scratch "
                     "(at most %lld)", (long long)c->l,
                     kScratchFloats, (long long)((cap - kBM) / kBM));
-    // The split pass, where a panel of packed rows and its partial sums fit
-    // the scratch: chunks of `rows` packed rows first, the partial sums in
-    // what is left. Of the chunk sizes that fit, the one with the least
-    // predicted time is taken (larger chunks leave room for fewer splits).
-    if (use_split(c, n_z) &&
-        (int64_t)packed_bytes(c, kQPanel) / 4 + kQPanel * L <= cap) {
+    // The split pass, where the scratch holds a panel of packed rows, its
+    // partial sums and (beyond kMaxFusedTiles label tiles) its kernel values
+    // with at least 64 panels of centres. Of the chunk sizes that fit, the
+    // one with the least predicted time is taken (larger chunks leave room
+    // for fewer splits).
+    if (use_split(c, n_z)) {
+        const bool stored = c->lt16 > kMaxFusedTiles;
         SplitPlan plan{};
         int64_t rows = 0;
         double best = 1e300;
         for (int64_t panels = std::min<int64_t>(ceil_div(n_z, kQPanel), 512);; panels = ceil_div(panels, 2)) {
             const int64_t nq = std::min<int64_t>(n_z, panels * kQPanel);
             const int64_t left = cap - (int64_t)packed_bytes(c, nq) / 4;
-            const int64_t max_sl = left > 0 ? left / (round_up(nq, kBM) * L) : 0;
-            if (max_sl >= 1) {
-                const SplitPlan pl = split_plan(nq, c->n, c->lt16, c->kind,
-                                                (int)std::min<int64_t>(max_sl, 256));
+            // (stored: half of the rest for the kernel values)
+            const int64_t kfl = stored ? left / 2 : 0;
+            const int64_t max_sl = left > 0 ? (left - kfl) / (round_up(nq, kBM) * L) : 0;
+            if (max_sl >= 1 &&
+                (!stored || 4 * kfl >= kvalue_bytes(nq, std::min<int64_t>(c->n, 64 * kCPanel)))) {
+                const SplitPlan pl = plan_split(c, nq, max_sl, (size_t)kfl * 4);
                 const double t = pl.cost * (double)ceil_div(n_z, nq);
                 if (t < best) {
                     best = t;
@@ -1108,17 +1187,19 @@ int ep_predict_noalloc(ep_ctx* c, const float* Z, int64_t n_z, float* out) {
             if (panels == 1) break;
         }
         char* q = reinterpret_cast<char*>(c->scratch);
-        for (int64_t z0 = 0; z0 < n_z; z0 += rows) {
+        for (int64_t z0 = 0; rows > 0 && z0 < n_z; z0 += rows) {
             const int64_t nq = std::min(rows, n_z - z0);
             const int64_t rows_pad = round_up(nq, kBM);
             float* part = c->scratch + packed_bytes(c, nq) / 4;
+            char* kbuf = reinterpret_cast<char*>(part + (int64_t)plan.splits * rows_pad * L);
             int rc = pack_queries(c, Z + z0 * c->d, nullptr, nq, q, false);
             if (rc) return rc;
-            if ((rc = run_split(c, q, nullptr, nq, plan, part, rows_pad, false, false))) return rc;
+            if ((rc = run_split(c, q, nullptr, nq, plan, part, rows_pad, kbuf, false, false)))
+                return rc;
             HIP_TRY(launch_reduce_rows(part, plan.splits, rows_pad, L, nq, c->l, out + z0 * c->l,
                                        c->l, st));
         }
-        return EP_OK;
+        if (rows > 0) return EP_OK;
     }
     for (int64_t z0 = 0; z0 < n_z;) {
         int64_t tq = std::min<int64_t>(ceil_div(n_z - z0, kBM), 512);

@@ -162,15 +162,39 @@ struct SplitArgs {
     const int* kpos;           // as in KmvArgs
     float* ksb;
     int64_t ldk;
+    int64_t c_base;            // global row id of the first centre
+    char* kplanes;             // lt = 0: the kernel values' planes,
+    int64_t kgroups;           //   kgroups 32-centre groups per 16 queries
 };
 struct SplitPlan {
     int splits;
     int64_t tps;               // centre panels per split
     double cost;               // predicted time, in panels of one workgroup
+    int64_t chunk = 0;         // centre panels per chunk of stored kernel values
 };
 constexpr int kMaxFusedTiles = 10;   // label tiles whose accumulators fit the fused pass
 SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, int max_slices);
 hipError_t split_launch(SplitArgs a, const SplitPlan& p, hipStream_t s);
+
+// out[split][q, j] (+)= sum of K[q, c] W[c, j] over a chunk's centres, from
+// the planes that split_launch stored with lt = 0.
+struct WmulArgs {
+    const char* K;
+    int64_t kgroups;           // 32-centre groups per 16 queries of the buffer
+    int64_t nq;
+    const char* W;             // weight planes from the chunk's first group on
+    int lt;                    // label tiles of 16
+    int groups;                // 32-centre groups of the chunk
+    float* out;                // partials [splits][out_rows][ldw]
+    int64_t out_rows;
+    int64_t ldw;
+    int accumulate;            // add to what out holds
+    int splits;                // (set by the launch)
+    int64_t gps;
+};
+// tps: 32-centre groups per split
+SplitPlan wmul_plan(int64_t nq, int64_t groups, int64_t lt, int max_slices);
+hipError_t wmul_launch(WmulArgs a, const SplitPlan& p, hipStream_t s);
 
 // Thin products of steps 4-5 (thin_gemm.hip):
 //   C[p] = sum over depth chunk p of A(i, kk) B(kk, j), i < M, j < N,

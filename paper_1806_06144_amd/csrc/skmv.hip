@@ -159,6 +159,9 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float* W, int64
 
 // One workgroup = 4 waves owns 64 QB queries (QB blocks of 16 per wave) and a
 // contiguous range of centre panels of 128 rows, walked panel by panel.
+// LT = 0: the kernel values themselves are the result, written as the operand
+// planes of wmul_kernel (16 queries x 32 centres, three bf16 planes; those of
+// odd 32-centre groups negated).
 template <int KIND, int LT, int QB>
 __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
     constexpr int kWQ = 16 * QB;                     // queries per wave
@@ -198,7 +201,7 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
         qn[b] = qmeta[q];
         iq2[b] = -2.f * qmeta[kQPanel + q];
         const int64_t row = row0 + 16 * b + col;
-        qid[b] = p.qid && row < p.nq ? (int)p.qid[row] : -1;
+        qid[b] = p.qid && row < p.nq ? (int)(p.qid[row] - p.c_base) : -1;
     }
 
     auto slot_of = [&](auto tag) -> uintx4* {
@@ -233,7 +236,7 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
     };
 
     floatx4 sacc[8][QB];
-    floatx4 oacc[LT][QB];
+    floatx4 oacc[LT > 0 ? LT : 1][QB];
 #pragma unroll
     for (int c = 0; c < 8; ++c)
 #pragma unroll
@@ -365,19 +368,19 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
                 }
             }
         }
-        const __amdgpu_buffer_rsrc_t wrs =
+        [[maybe_unused]] const __amdgpu_buffer_rsrc_t wrs =
             make_rsrc(reinterpret_cast<const float*>(p.W + (int64_t)t * 4 * LT * 3 * kFragBytes),
                       (int64_t)4 * LT * 3 * kFragBytes);
         // (the scheduling barriers keep the compiler from lengthening the
         // weights' lifetimes until they no longer fit the registers)
-        auto load_w = [&](uintx4 (&w)[3], int f) {
+        [[maybe_unused]] auto load_w = [&](uintx4 (&w)[3], int f) {
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl)
                 w[pl] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(
                                                        wrs, lane * 16, (f * 3 + pl) * kFragBytes, 0));
         };
-        uintx4 wf[2][3];
-        load_w(wf[0], 0);
+        [[maybe_unused]] uintx4 wf[2][3];
+        if constexpr (LT > 0) load_w(wf[0], 0);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             uintx4 kf[QB][3];
@@ -409,6 +412,16 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
                 sacc[2 * u + 1][b] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (LT == 0) {
+#pragma unroll
+                for (int b = 0; b < QB; ++b) {
+                    char* o = p.kplanes + ((row0 / 16 + b) * p.kgroups + 4 * t + u) * 3 * kFragBytes +
+                              lane * 16;
+#pragma unroll
+                    for (int pl = 0; pl < 3; ++pl)
+                        *reinterpret_cast<uintx4*>(o + pl * kFragBytes) = kf[b][pl];
+                }
+            }
 #pragma unroll
             for (int j = 0; j < LT; ++j) {
                 const int f = u * LT + j;
@@ -435,7 +448,7 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
             }
         }
     }
-    if (!live) return;
+    if (LT == 0 || !live) return;
     // element i of tile j, block b: label 16 j + 4 g + i, query 16 b + col
     float* o = p.out + ((int64_t)split * p.out_rows + row0) * p.ldw + 4 * g;
 #pragma unroll
@@ -445,11 +458,151 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
             *reinterpret_cast<floatx4*>(o + (int64_t)(16 * b + col) * p.ldw + 16 * j) = oacc[j][b];
 }
 
+// ---- contraction of stored kernel values ------------------------------------
+
+// out[q, :] (+)= sum_c K[q, c] W[c, :] over the 32-centre groups of a split,
+// from the planes that skmv_kernel<KIND, 0, QB> stored and the planes of W.
+// One workgroup = 4 waves owns 128 queries (32 per wave) x 128 labels (8
+// tiles). The weights, which the waves share, pass through three LDS slots
+// two groups ahead; each wave reads its kernel values from the L2 one group
+// ahead. Accumulators for more than 160 labels do not fit beside those of the
+// distances, so the kernel values (6 bytes each) make a round trip through
+// memory: at 160000 x 2048, 1000 labels, 1601 queries the two launches take
+// 2.83 + 2.48 ms, 1.25 PFLOP/s of 16-bit products each, the rate a large
+// library product reaches here (one float32 pass: 12.7 ms).
+constexpr int kWTiles = 8;                           // label tiles per workgroup
+constexpr int kWQ = 128;                             // queries per workgroup
+constexpr int kWSlotQuads = kWTiles * 3 * 64;
+
+__global__ void __launch_bounds__(kSThreads, 2) wmul_kernel(WmulArgs p) {
+    __shared__ uintx4 ws0[kWSlotQuads];
+    __shared__ uintx4 ws1[kWSlotQuads];
+    __shared__ uintx4 ws2[kWSlotQuads];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, g = lane >> 4;
+    // The label panels of one (query tile, split) share their kernel values,
+    // so they run on one XCD (workgroups go to the 8 XCDs round robin).
+    const int np = (p.lt + kWTiles - 1) / kWTiles;
+    const int tq = (int)((p.nq + kWQ - 1) / kWQ);
+    const int item = ((int)blockIdx.x >> 3) / np * 8 + ((int)blockIdx.x & 7);
+    const int panel = ((int)blockIdx.x >> 3) % np;
+    const int split = item / tq;
+    const int qtile = item - split * tq;
+    if (split >= p.splits) return;
+    const int g0 = (int)min((int64_t)p.groups, split * p.gps);
+    const int n = (int)min((int64_t)p.groups, g0 + p.gps) - g0;
+    const int nj = min(kWTiles, p.lt - panel * kWTiles);   // label tiles of this panel
+
+    const int64_t row0 = min((int64_t)qtile * kWQ + wave * 32, (p.nq + 31) / 32 * 32 - 32);
+    const bool live = (int64_t)qtile * kWQ + wave * 32 < p.nq;
+    const char* kbase = p.K + (row0 / 16 * p.kgroups + g0) * 3 * kFragBytes;
+    const int64_t kstep = p.kgroups * 3 * kFragBytes;      // next 16 queries
+    const char* wbase = p.W + ((int64_t)g0 * p.lt + panel * kWTiles) * 3 * kFragBytes;
+    const int64_t wstep = (int64_t)p.lt * 3 * kFragBytes;
+
+    auto slot_of = [&](auto tag) -> uintx4* {
+        constexpr int S = decltype(tag)::value % 3;
+        if constexpr (S == 0) return ws0;
+        else if constexpr (S == 1) return ws1;
+        else return ws2;
+    };
+    auto dma = [&](auto tag, int i) {
+        uintx4* base = slot_of(tag);
+        const __amdgpu_buffer_rsrc_t wrs =
+            make_rsrc(reinterpret_cast<const float*>(wbase + i * wstep), nj * 3 * kFragBytes);
+        // (fragments past the panel's last tile read as zero)
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            const int at = 6 * wave + f;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lds_void*)(base + at * 64), 16,
+                                                     lane * 16 + at * kFragBytes, 0, 0, 0);
+        }
+    };
+    uintx4 kf[2][2][3];
+    auto kload = [&](uintx4 (&k)[2][3], int i) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const __amdgpu_buffer_rsrc_t krs = make_rsrc(
+                reinterpret_cast<const float*>(kbase + b * kstep + (int64_t)i * 3 * kFragBytes), 3 * kFragBytes);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                k[b][pl] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                          krs, lane * 16, pl * kFragBytes, 0));
+        }
+    };
+    floatx4 oacc[kWTiles][2];
+    // element i of tile j, block b: label 16 j + 4 g + i, query 16 b + col
+    float* o = p.out + ((int64_t)split * p.out_rows + row0) * p.ldw + panel * kWTiles * 16 + 4 * g;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int j = 0; j < kWTiles; ++j)
+            oacc[j][b] = p.accumulate && j < nj
+                             ? *reinterpret_cast<const floatx4*>(o + (int64_t)(16 * b + col) * p.ldw + 16 * j)
+                             : floatx4{0.f, 0.f, 0.f, 0.f};
+
+    auto step = [&](auto tag, int i) {
+        constexpr int S = decltype(tag)::value;
+        if (i + 1 < n) kload(kf[(S + 1) & 1], i + 1);
+        if (i + 2 < n) dma(std::integral_constant<int, (S + 2) % 3>{}, i + 2);
+        const uintx4* ws = slot_of(tag);
+        const uintx4 (&k)[2][3] = kf[S & 1];
+        uintx4 w[2][3];
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) w[0][pl] = ws[pl * 64 + lane];
+#pragma unroll
+        for (int j = 0; j < kWTiles; ++j) {
+            if (j >= nj) break;
+            if (j + 1 < kWTiles) {
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) w[(j + 1) & 1][pl] = ws[((j + 1) * 3 + pl) * 64 + lane];
+            }
+            // from zero, smallest first, the sign turned every other group
+            // (the stored planes of odd groups are negated): see skmv_kernel
+            constexpr int wp[6] = {2, 0, 1, 1, 0, 0}, kq[6] = {0, 2, 1, 0, 1, 0};
+            floatx4 t[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int x = 0; x < 6; ++x)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) t[b] = mfma_bf16(w[j & 1][wp[x]], k[b][kq[x]], t[b]);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) oacc[j][b] += S & 1 ? -t[b] : t[b];
+        }
+        // the next group's weights, fetched a step ago, are in LDS for all
+        if (i + 2 < n) wg_barrier<12>();
+        else wg_barrier<0>();
+    };
+    if (n > 0) {
+        dma(std::integral_constant<int, 0>{}, 0);
+        if (n > 1) dma(std::integral_constant<int, 1>{}, 1);
+        kload(kf[0], 0);
+        wg_barrier<0>();
+        for (int i = 0; i < n; i += 6) {
+            step(std::integral_constant<int, 0>{}, i);
+            if (i + 1 < n) step(std::integral_constant<int, 1>{}, i + 1);
+            if (i + 2 < n) step(std::integral_constant<int, 2>{}, i + 2);
+            if (i + 3 < n) step(std::integral_constant<int, 3>{}, i + 3);
+            if (i + 4 < n) step(std::integral_constant<int, 4>{}, i + 4);
+            if (i + 5 < n) step(std::integral_constant<int, 5>{}, i + 5);
+        }
+    }
+    if (!live) return;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int j = 0; j < kWTiles; ++j)
+            if (j < nj)
+                *reinterpret_cast<floatx4*>(o + (int64_t)(16 * b + col) * p.ldw + 16 * j) = oacc[j][b];
+}
+
 typedef void (*SplitFn)(SplitArgs);
 
 template <int KIND>
 SplitFn fused_fn(int lt) {                          // (query blocks: split_rows)
     switch (lt) {
+        case 0: return skmv_kernel<KIND, 0, 4>;
         case 1: return skmv_kernel<KIND, 1, 4>;
         case 2: return skmv_kernel<KIND, 2, 2>;
         case 3: return skmv_kernel<KIND, 3, 2>;
@@ -464,7 +617,7 @@ SplitFn fused_fn(int lt) {                          // (query blocks: split_rows
 }
 
 // Queries per workgroup of the fused pass with lt label tiles.
-int split_rows(int64_t lt) { return lt <= 1 ? 256 : 128; }
+int split_rows(int64_t lt) { return lt <= 1 ? 256 : 128; }   // (0: kernel values)
 
 int split_slots(SplitFn fn) {
     int dev = 0, cus = 256, per = 0;
@@ -535,6 +688,40 @@ SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, int max_slice
         }
     }
     return best;
+}
+
+SplitPlan wmul_plan(int64_t nq, int64_t groups, int64_t lt, int max_slices) {
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        cus = 256;
+    const int64_t slots = 2 * (int64_t)cus;          // (launch bounds and LDS)
+    const int64_t tiles = ceil_div(std::max<int64_t>(nq, 1), kWQ) * ceil_div(lt, kWTiles);
+    const int64_t quads = ceil_div(std::max<int64_t>(groups, 1), 4);
+    SplitPlan best{1, 4 * quads, 0.0};
+    double bt = 1e300;
+    for (int64_t P = 1; P <= quads && P <= max_slices; ++P) {
+        const int64_t per = ceil_div(quads, P);
+        if (ceil_div(quads, per) != P) continue;
+        // (partial sums in and out cost about two groups' products)
+        const double t = (double)ceil_div(tiles * P, slots) * (4.0 * (double)per + 2.0);
+        if (t < bt) {
+            bt = t;
+            best.splits = (int)P;
+            best.tps = 4 * per;
+            best.cost = t;
+        }
+    }
+    return best;
+}
+
+hipError_t wmul_launch(WmulArgs a, const SplitPlan& p, hipStream_t s) {
+    a.splits = p.splits;
+    a.gps = p.tps;
+    const int64_t items = ceil_div(std::max<int64_t>(a.nq, 1), kWQ) * p.splits;
+    hipLaunchKernelGGL(wmul_kernel, dim3((unsigned)(round_up(items, 8) * ceil_div(a.lt, kWTiles))),
+                       dim3(kSThreads), 0, s, a);
+    return hipGetLastError();
 }
 
 hipError_t split_launch(SplitArgs a, const SplitPlan& p, hipStream_t s) {

@@ -50,6 +50,11 @@ CASES = [
     ("gaussian", 300000, 7, 3, 65), ("laplacian", 128 * 9 - 2, 416, 80, 300),
     ("gaussian", 128 * 19 + 64, 224, 65, 250), ("laplacian", 128 * 2 + 1, 2500, 10, 320),
     ("gaussian", 100, 8200, 20, 200),
+    # beyond 160 labels the kernel values are stored: label panels of 128
+    # full, one tile past, one label past; several centre groups per split
+    ("gaussian", 128 * 41 + 1, 100, 161, 250), ("laplacian", 128 * 60, 70, 256, 257),
+    ("gaussian", 128 * 33 + 65, 135, 257, 300), ("gaussian", 128 * 8 - 1, 1040, 1100, 129),
+    ("laplacian", 70000, 31, 500, 30),
 ]
 
 
@@ -83,7 +88,7 @@ def test_predict_edges(kernel, n, d, l, n_z, law):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("m", [63, 64, 65, 128, 129, 255, 256, 257, 400])
-@pytest.mark.parametrize("d,l", [(699, 12), (700, 30)])
+@pytest.mark.parametrize("d,l", [(699, 12), (700, 30), (703, 200)])
 def test_step_batch_edges(m, d, l):
     """Own centres (k = 1), kept subsample columns and the planes of alpha
     after each update, over two steps."""
@@ -105,3 +110,27 @@ def test_step_batch_edges(m, d, l):
             assert rel(F, F_o) < TOL_STEP
             a_o = a_n
         assert rel(g.alpha() - a0, a_o - a0) < TOL_STEP
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("l", [9, 300])
+@pytest.mark.parametrize("n_z", [3, 700])
+def test_noalloc_in_chunks(l, n_z):
+    """ep_predict_noalloc on the split pass, whose scratch holds the packed
+    rows, the partial sums and (300 labels) the kernel values of a chunk."""
+    import paper_1806_06144_amd as ep
+    n, d, bw = 40001, 90, bw32(9.0)
+    rng = np.random.default_rng(n_z + l)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    Z = rng.standard_normal((n_z, d)).astype(np.float32)
+    a = rng.standard_normal((n, l)).astype(np.float32)
+    assert -(-n_z // 64) * 64 * n * d > 2 ** 27
+    with Gpu(X, l, "gaussian", bw, 20, 2, np.arange(20)) as g:
+        g.set_alpha(a)
+        out = g.torch.full((n_z, l), float("nan"), dtype=g.torch.float32, device=g.dev)
+        ep.ep_predict_noalloc(g.ctx, g.t(Z), n_z, out)
+        ep.ep_sync(g.ctx)
+        P = out.cpu().numpy()
+    P_o = oracle.predict(X.astype(np.float64), a.astype(np.float64), Z.astype(np.float64),
+                         oracle.GAUSSIAN, bw)
+    assert np.max(np.abs(P - P_o) / _bound(X, Z, a, "gaussian", bw)) <= 1.0
