@@ -170,6 +170,7 @@ struct SplitPlan {
     int splits;
     int64_t tps;               // centre panels per split
     double cost;               // predicted time, in panels of one workgroup
+    int cw = 8;                // centre blocks per wave
     int64_t chunk = 0;         // centre panels per chunk of stored kernel values
 };
 constexpr int kMaxFusedTiles = 10;   // label tiles whose accumulators fit the fused pass
@@ -246,15 +247,18 @@ hipError_t launch_gather_rows(const float* X, int64_t n, int64_t d, const float*
                               float* out, float* out_norms, int* err, hipStream_t s);
 // R gets r_rows rows (zero beyond m) so that it can serve as the weights of
 // a fused pass whose centres are the batch rows. `planes` (may be NULL): the
-// split planes of alpha, updated with it (lt label tiles).
+// split planes of alpha, updated with it (lt label tiles). `wide`: slices may
+// be summed in groups (faster for few elements, another order of addition);
+// not for the float32 pass, whose results keep the order they had.
 hipError_t launch_reduce_residual(const float* part, int slices, int64_t rows_pad,
                                   int64_t ldw, int64_t m, int64_t l, const float* y,
                                   float* f_out, float* R, int64_t r_rows, float* alpha,
                                   int64_t n, const int64_t* t, float coef,
-                                  unsigned short* planes, int64_t lt, hipStream_t s);
+                                  unsigned short* planes, int64_t lt, bool wide,
+                                  hipStream_t s);
 hipError_t launch_reduce_rows(const float* part, int slices, int64_t rows_pad,
                               int64_t ldw, int64_t rows, int64_t cols, float* out,
-                              int64_t ldo, hipStream_t s);
+                              int64_t ldo, bool wide, hipStream_t s);
 hipError_t launch_subsample_kernel_f64(const float* Xs, int64_t s, int64_t d,
                                        int kind, double bandwidth, double* Ks,
                                        hipStream_t st);

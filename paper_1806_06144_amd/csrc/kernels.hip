@@ -53,22 +53,72 @@ __global__ void __launch_bounds__(256) gather_rows_kernel(const float* X, int64_
     if (threadIdx.x == 0) out_norms[b] = norms[src];
 }
 
+// Sum of `slices` values `stride` floats apart, in slice order. One element
+// may have 256 slices; read one at a time they cost their latency each (54 us
+// for one row of 10 labels), so sixteen are in flight before the (ordered)
+// additions: 7 us.
+__device__ __forceinline__ float sum_slices(const float* p, int slices, int64_t stride) {
+    float f = 0.f;
+    int sl = 0;
+    for (; sl + 16 <= slices; sl += 16) {
+        float v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = p[(int64_t)(sl + i) * stride];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) f += v[i];
+    }
+    for (; sl + 4 <= slices; sl += 4) {
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = p[(int64_t)(sl + i) * stride];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f += v[i];
+    }
+    for (; sl < slices; ++sl) f += p[(int64_t)sl * stride];
+    return f;
+}
+
+// The same sum with the slices dealt to G lanes of a block (element e = lane
+// % (256 / G)), each a contiguous range, whose sums are added in order: where
+// the elements alone are too few to hide the loads' latency. Every thread of
+// the block calls it; `ok` lanes hold an element.
+template <int G>
+__device__ __forceinline__ float sum_slices_wide(const float* p, int slices, int64_t stride,
+                                                 bool ok) {
+    if constexpr (G == 1) {
+        return ok ? sum_slices(p, slices, stride) : 0.f;
+    } else {
+        constexpr int E = 256 / G;
+        __shared__ float s[G][E];
+        const int e = threadIdx.x % E, g = threadIdx.x / E;
+        const int per = (slices + G - 1) / G;
+        const int lo = min(slices, g * per);
+        s[g][e] = ok ? sum_slices(p + (int64_t)lo * stride, min(slices, lo + per) - lo, stride) : 0.f;
+        __syncthreads();
+        float f = 0.f;
+#pragma unroll
+        for (int i = 0; i < G; ++i) f += s[i][e];
+        return f;
+    }
+}
+
 // F = sum of partial slices; R = F - y_b; alpha[t] -= coef * R (step 3).
 // Rows >= m and columns >= l of R are written as zero.
+template <int G>
 __global__ void __launch_bounds__(256) reduce_residual_kernel(
     const float* part, int slices, int64_t rows_pad, int64_t ldw, int64_t m, int64_t l,
     const float* y, float* f_out, float* R, int64_t r_rows, float* alpha, int64_t n,
     const int64_t* t, float coef, unsigned short* planes, int64_t lt) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= r_rows * ldw) return;
+    const int64_t e = (int64_t)blockIdx.x * (256 / G) + threadIdx.x % (256 / G);
     const int64_t b = e / ldw;
     const int64_t c = e - b * ldw;
-    if (b >= m || c >= l) {
-        R[e] = 0.f;
+    const bool ok = b < m && c < l;
+    const float f = sum_slices_wide<G>(part + b * ldw + c, slices, rows_pad * ldw, ok);
+    if (threadIdx.x >= 256 / G) return;
+    if (!ok) {
+        if (b < r_rows) R[e] = 0.f;
         return;
     }
-    float f = 0.f;
-    for (int sl = 0; sl < slices; ++sl) f += part[((int64_t)sl * rows_pad + b) * ldw + c];
     const float r = f - y[b * l + c];
     if (f_out) f_out[b * l + c] = f;
     R[e] = r;
@@ -80,17 +130,17 @@ __global__ void __launch_bounds__(256) reduce_residual_kernel(
     }
 }
 
+template <int G>
 __global__ void __launch_bounds__(256) reduce_rows_kernel(const float* part, int slices,
                                                           int64_t rows_pad, int64_t ldw,
                                                           int64_t rows, int64_t cols,
                                                           float* out, int64_t ldo) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= rows * cols) return;
+    const int64_t e = (int64_t)blockIdx.x * (256 / G) + threadIdx.x % (256 / G);
     const int64_t b = e / cols;
     const int64_t c = e - b * cols;
-    float f = 0.f;
-    for (int sl = 0; sl < slices; ++sl) f += part[((int64_t)sl * rows_pad + b) * ldw + c];
-    out[b * ldo + c] = f;
+    const bool ok = e < rows * cols;
+    const float f = sum_slices_wide<G>(part + b * ldw + c, slices, rows_pad * ldw, ok);
+    if (ok && threadIdx.x < 256 / G) out[b * ldo + c] = f;
 }
 
 // K_s[i, j] = k(x_ri, x_rj) in float64 from direct coordinate differences.
@@ -162,6 +212,10 @@ __global__ void __launch_bounds__(256) fill_kernel(float* p, int64_t count, floa
     if (e < count) p[e] = v;
 }
 
+// Up to this many elements (one per resident thread or fewer) the reductions
+// deal an element's slices to eight lanes.
+constexpr int64_t kWideElems = 1 << 18;
+
 inline unsigned blocks_for(int64_t count, int per = 256) {
     return (unsigned)((count + per - 1) / per);
 }
@@ -188,20 +242,29 @@ hipError_t launch_gather_rows(const float* X, int64_t n, int64_t d, const float*
 hipError_t launch_reduce_residual(const float* part, int slices, int64_t rows_pad, int64_t ldw,
                                   int64_t m, int64_t l, const float* y, float* f_out, float* R,
                                   int64_t r_rows, float* alpha, int64_t n, const int64_t* t,
-                                  float coef, unsigned short* planes, int64_t lt,
+                                  float coef, unsigned short* planes, int64_t lt, bool wide,
                                   hipStream_t s) {
-    hipLaunchKernelGGL(reduce_residual_kernel, dim3(blocks_for(r_rows * ldw)), dim3(256), 0, s,
-                       part, slices, rows_pad, ldw, m, l, y, f_out, R, r_rows, alpha, n, t, coef,
-                       planes, lt);
+    if (wide && slices >= 32 && m * l <= kWideElems)
+        hipLaunchKernelGGL(reduce_residual_kernel<8>, dim3(blocks_for(r_rows * ldw, 32)), dim3(256),
+                           0, s, part, slices, rows_pad, ldw, m, l, y, f_out, R, r_rows, alpha, n,
+                           t, coef, planes, lt);
+    else
+        hipLaunchKernelGGL(reduce_residual_kernel<1>, dim3(blocks_for(r_rows * ldw)), dim3(256), 0,
+                           s, part, slices, rows_pad, ldw, m, l, y, f_out, R, r_rows, alpha, n, t,
+                           coef, planes, lt);
     return hipGetLastError();
 }
 
 hipError_t launch_reduce_rows(const float* part, int slices, int64_t rows_pad, int64_t ldw,
                               int64_t rows, int64_t cols, float* out, int64_t ldo,
-                              hipStream_t s) {
+                              bool wide, hipStream_t s) {
     if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(reduce_rows_kernel, dim3(blocks_for(rows * cols)), dim3(256), 0, s, part,
-                       slices, rows_pad, ldw, rows, cols, out, ldo);
+    if (wide && slices >= 32 && rows * cols <= kWideElems)
+        hipLaunchKernelGGL(reduce_rows_kernel<8>, dim3(blocks_for(rows * cols, 32)), dim3(256), 0, s,
+                           part, slices, rows_pad, ldw, rows, cols, out, ldo);
+    else
+        hipLaunchKernelGGL(reduce_rows_kernel<1>, dim3(blocks_for(rows * cols)), dim3(256), 0, s,
+                           part, slices, rows_pad, ldw, rows, cols, out, ldo);
     return hipGetLastError();
 }
 

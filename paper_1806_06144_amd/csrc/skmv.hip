@@ -46,10 +46,10 @@ constexpr int kSlotQuads = kCPanel / 16 * 2 * 64;    // 16-byte quads of one 32-
 // row maxima first unless they are given, then the two scaled fp16 planes.
 // Rows past `rows` and gathered rows out of [0, n) are zero (norm 0, scale 1).
 template <bool VEC>
-__global__ void __launch_bounds__(256) pack_rows_kernel(PackArgs p) {
+__global__ void __launch_bounds__(1024) pack_rows_kernel(PackArgs p) {
     __shared__ float s_norm[16], s_inv[16], s_scale[16];
     __shared__ int64_t s_row[16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
     const int64_t tile = blockIdx.x;
     if (tid < 16) {
         const int64_t b = tile * 16 + tid;
@@ -69,7 +69,7 @@ __global__ void __launch_bounds__(256) pack_rows_kernel(PackArgs p) {
     }
     __syncthreads();
     if (!p.norms_in) {
-        for (int r = wave; r < 16; r += 4) {
+        for (int r = wave; r < 16; r += waves) {
             const int64_t src = s_row[r];
             double acc = 0.0;
             float mx = 0.f;
@@ -117,7 +117,7 @@ __global__ void __launch_bounds__(256) pack_rows_kernel(PackArgs p) {
     const float* x = p.X + (src >= 0 ? src : 0) * p.d;
     const int64_t t_panel = p.P / 16;
     char* out = p.out + (tile / t_panel) * p.panel + (tile % t_panel) * 2 * kFragBytes + lane * 16;
-    for (int64_t ks = wave; ks < p.nk; ks += 4) {
+    for (int64_t ks = wave; ks < p.nk; ks += waves) {
         const int64_t c0 = ks * 32 + 8 * g;
         const float sck = ks >= p.neg0 && ks < p.neg1 ? -sc : sc;
         float v[8];
@@ -157,15 +157,27 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float* W, int64
 
 // ---- the fused pass --------------------------------------------------------
 
-// One workgroup = 4 waves owns 64 QB queries (QB blocks of 16 per wave) and a
-// contiguous range of centre panels of 128 rows, walked panel by panel.
+// One workgroup = 4 waves owns a contiguous range of centre panels of 128
+// rows, walked panel by panel, for a tile of queries: the waves form 8 / CW
+// groups of CW blocks of 16 centres by CW / 2 groups of QB blocks of 16
+// queries. CW = 8 gives every wave all centres of the panel and queries of
+// its own (64 QB in all); CW = 2 gives the waves a quarter of the panel each
+// and the same 16 QB queries, for calls of few rows, where otherwise three
+// waves of four would idle: one row against 60000 x 784 80 -> 35 us (the
+// packed centres at 5.4 TB/s), 48 rows against 1.1 M x 440 with 144 labels
+// 1130 -> 595 us (centres and weights at 4.9 TB/s: both at the rate of a
+// large copy). For many queries CW = 4 is slower than CW = 8: it moves the
+// same centres for half the queries (10000 rows against 60000 x 784, 2.68
+// against 2.11 ms).
 // LT = 0: the kernel values themselves are the result, written as the operand
 // planes of wmul_kernel (16 queries x 32 centres, three bf16 planes; those of
 // odd 32-centre groups negated).
-template <int KIND, int LT, int QB>
+template <int KIND, int LT, int QB, int CW>
 __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
+    static_assert(CW == 8 || LT > 0, "stored kernel values: CW = 8");
     constexpr int kWQ = 16 * QB;                     // queries per wave
-    constexpr int kSQ = 4 * kWQ;
+    constexpr int kSQ = CW / 2 * kWQ;
+    constexpr int kCG = 8 / CW;                      // centre groups
     __shared__ uintx4 xs0[kSlotQuads];
     __shared__ uintx4 xs1[kSlotQuads];
     __shared__ uintx4 xs2[kSlotQuads];
@@ -186,9 +198,11 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
 
     // this wave's queries, inside one packed panel (a wave past the last
     // query only helps to move the centres)
-    const int64_t row0 = min((int64_t)qtile * kSQ + wave * kWQ,
+    const int wq = wave / kCG, wc = wave % kCG;
+    [[maybe_unused]] const float sgn = wc & 1 ? -1.f : 1.f;
+    const int64_t row0 = min((int64_t)qtile * kSQ + wq * kWQ,
                              (p.nq + kQPanel - 1) / kQPanel * kQPanel - kWQ);
-    const bool live = (int64_t)qtile * kSQ + wave * kWQ < p.nq;
+    const bool live = (int64_t)qtile * kSQ + wq * kWQ < p.nq;
     const char* qbase = p.Q + row0 / kQPanel * p.q_panel;
     const int qb0 = (int)(row0 % kQPanel) / 16;
     const __amdgpu_buffer_rsrc_t qrs = make_rsrc(reinterpret_cast<const float*>(qbase), p.q_panel);
@@ -235,10 +249,10 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
                                 qrs, lane * 16, (ks * 8 + (qb0 + i) * 2 + pl) * kFragBytes, 0));
     };
 
-    floatx4 sacc[8][QB];
+    floatx4 sacc[CW][QB];
     floatx4 oacc[LT > 0 ? LT : 1][QB];
 #pragma unroll
-    for (int c = 0; c < 8; ++c)
+    for (int c = 0; c < CW; ++c)
 #pragma unroll
         for (int b = 0; b < QB; ++b) sacc[c][b] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -251,20 +265,20 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
         // the queries' planes change sign here (sign_steps)
         if (ks == p.neg0 || ks == p.neg1) {
 #pragma unroll
-            for (int c = 0; c < 8; ++c)
+            for (int c = 0; c < CW; ++c)
 #pragma unroll
                 for (int i = 0; i < QB; ++i) sacc[c][i] = -sacc[c][i];
         }
         if (ks + 1 < nk) qload(bq[(S & 1) ^ 1], ks + 1);
         if (ks + 3 < nk) dma(std::integral_constant<int, (S + 3) & 3>{}, crs, ks + 3);
-        const uintx4* xs = slot_of(tag);
+        const uintx4* xs = slot_of(tag) + wc * CW * 128;
         const uintx4 (&b)[QB][2] = bq[S & 1];
         uintx4 a[2][2];
         a[0][0] = xs[lane];
         a[0][1] = xs[64 + lane];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            if (c < 7) {
+        for (int c = 0; c < CW; ++c) {
+            if (c < CW - 1) {
                 a[(c + 1) & 1][0] = xs[(2 * c + 2) * 64 + lane];
                 a[(c + 1) & 1][1] = xs[(2 * c + 3) * 64 + lane];
             }
@@ -331,15 +345,16 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
 #pragma unroll
             for (int b = 0; b < QB; ++b) {
                 const int r = qid[b] - t * kCPanel;
-                const bool in = qid[b] >= 0 && r >= 0 && r < kCPanel && ((r >> 2) & 3) == g;
-                rel[b] = in ? 4 * (r >> 4) + (r & 3) : -1;
+                const bool in = qid[b] >= 0 && r >= 0 && r < kCPanel && ((r >> 2) & 3) == g &&
+                                (r >> 4) / CW == wc;
+                rel[b] = in ? 4 * ((r >> 4) % CW) + (r & 3) : -1;
                 any |= in;
             }
             if (__any(any)) {
 #pragma unroll
                 for (int b = 0; b < QB; ++b)
 #pragma unroll
-                    for (int c = 0; c < 8; ++c)
+                    for (int c = 0; c < CW; ++c)
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
                             if (rel[b] == 4 * c + i) sacc[c][b][i] = __builtin_inff();
@@ -350,14 +365,15 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
             const uint64_t f0 = __ballot(kp[0] >= 0), f1 = __ballot(kp[1] >= 0);
             if (f0 | f1) {
 #pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const unsigned m16 = (unsigned)((c < 4 ? f0 : f1) >> (16 * (c & 3))) & 0xffffu;
+                for (int c = 0; c < CW; ++c) {
+                    const int cc = wc * CW + c;           // block of the panel
+                    const unsigned m16 = (unsigned)((cc < 4 ? f0 : f1) >> (16 * (cc & 3))) & 0xffffu;
                     if (!m16) continue;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         if (!(m16 & (0x1111u << i))) continue;
-                        const int at = 16 * c + 4 * g + i;
-                        const int pos = __shfl(kp[c >> 2], at & 63, 64);
+                        const int at = 16 * cc + 4 * g + i;
+                        const int pos = __shfl(cc < 4 ? kp[0] : kp[1], at & 63, 64);
                         const float cn = s_meta[at], ci = s_meta[kCPanel + at];
                         if (pos >= 0) {
                             float* o = p.ksb + pos * p.ldk + row0 + col;
@@ -380,14 +396,15 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
                                                        wrs, lane * 16, (f * 3 + pl) * kFragBytes, 0));
         };
         [[maybe_unused]] uintx4 wf[2][3];
-        if constexpr (LT > 0) load_w(wf[0], 0);
+        const int u0 = wc * (CW / 2);                    // 32-centre groups of this wave
+        if constexpr (LT > 0) load_w(wf[0], u0 * LT);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < CW / 2; ++u) {
             uintx4 kf[QB][3];
-            const floatx4 cn0 = *reinterpret_cast<const floatx4*>(&s_meta[32 * u + 4 * g]);
-            const floatx4 cn1 = *reinterpret_cast<const floatx4*>(&s_meta[32 * u + 16 + 4 * g]);
-            const floatx4 ci0 = *reinterpret_cast<const floatx4*>(&s_meta[kCPanel + 32 * u + 4 * g]);
-            const floatx4 ci1 = *reinterpret_cast<const floatx4*>(&s_meta[kCPanel + 32 * u + 16 + 4 * g]);
+            const floatx4 cn0 = *reinterpret_cast<const floatx4*>(&s_meta[32 * (u0 + u) + 4 * g]);
+            const floatx4 cn1 = *reinterpret_cast<const floatx4*>(&s_meta[32 * (u0 + u) + 16 + 4 * g]);
+            const floatx4 ci0 = *reinterpret_cast<const floatx4*>(&s_meta[kCPanel + 32 * (u0 + u) + 4 * g]);
+            const floatx4 ci1 = *reinterpret_cast<const floatx4*>(&s_meta[kCPanel + 32 * (u0 + u) + 16 + 4 * g]);
 #pragma unroll
             for (int b = 0; b < QB; ++b) {
                 float kv[8];
@@ -395,7 +412,10 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
                 for (int i = 0; i < 4; ++i) {
                     kv[i] = value(sacc[2 * u][b][i], cn0[i], ci0[i], b);
                     kv[4 + i] = value(sacc[2 * u + 1][b][i], cn1[i], ci1[i], b);
-                    if (u & 1) {                     // see the contraction below
+                    if (CW == 2) {                   // see the contraction below
+                        kv[i] *= sgn;
+                        kv[4 + i] *= sgn;
+                    } else if (u & 1) {
                         kv[i] = -kv[i];
                         kv[4 + i] = -kv[4 + i];
                     }
@@ -425,11 +445,12 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
 #pragma unroll
             for (int j = 0; j < LT; ++j) {
                 const int f = u * LT + j;
-                if (f + 1 < 4 * LT) load_w(wf[(f + 1) & 1], f + 1);
+                if (f + 1 < CW / 2 * LT) load_w(wf[(f + 1) & 1], u0 * LT + f + 1);
                 const uintx4 (&w)[3] = wf[f & 1];
                 // The products of 32 centres are summed from zero, smallest
                 // first, and added to the running sum outside the MFMA, every
-                // other time with both signs turned: an MFMA drops the
+                // other time (CW = 2: in every other wave) with both signs
+                // turned: an MFMA drops the
                 // addends' bits below the accumulator's last places towards
                 // minus infinity, which over the thousands of steps of a
                 // split shifts every sum the same way (7e-6 of the result at
@@ -443,10 +464,32 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
 #pragma unroll
                     for (int b = 0; b < QB; ++b) t[b] = mfma_bf16(w[wp[x]], kf[b][kq[x]], t[b]);
 #pragma unroll
-                for (int b = 0; b < QB; ++b) oacc[j][b] += u & 1 ? -t[b] : t[b];
+                for (int b = 0; b < QB; ++b) oacc[j][b] += CW == 2 ? sgn * t[b] : u & 1 ? -t[b] : t[b];
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+    }
+    if constexpr (LT > 0 && kCG > 1) {
+        // the centre groups' sums, in order, through LDS (the stage slots are
+        // free: every wave has passed the last panel's final barrier and no
+        // loads into them are in flight)
+        floatx4* sum0 = reinterpret_cast<floatx4*>(wq == 0 ? xs0 : xs2);
+        floatx4* sum1 = reinterpret_cast<floatx4*>(wq == 0 ? xs1 : xs3);
+        static_assert((LT + 1) / 2 * QB * 64 <= kSlotQuads, "half of the sums per slot");
+        for (int w = 0; w < kCG; ++w) {
+            __syncthreads();
+            if (wc == w) {
+#pragma unroll
+                for (int j = 0; j < LT; ++j)
+#pragma unroll
+                    for (int b = 0; b < QB; ++b) {
+                        floatx4& s = (j & 1 ? sum1 : sum0)[(j / 2 * QB + b) * 64 + lane];
+                        if (w > 0) oacc[j][b] = s + oacc[j][b];
+                        if (w < kCG - 1) s = oacc[j][b];
+                    }
+            }
+        }
+        if (wc != kCG - 1) return;
     }
     if (LT == 0 || !live) return;
     // element i of tile j, block b: label 16 j + 4 g + i, query 16 b + col
@@ -599,25 +642,32 @@ __global__ void __launch_bounds__(kSThreads, 2) wmul_kernel(WmulArgs p) {
 
 typedef void (*SplitFn)(SplitArgs);
 
-template <int KIND>
-SplitFn fused_fn(int lt) {                          // (query blocks: split_rows)
+template <int KIND, int CW>
+SplitFn fused_fn(int lt) {
     switch (lt) {
-        case 0: return skmv_kernel<KIND, 0, 4>;
-        case 1: return skmv_kernel<KIND, 1, 4>;
-        case 2: return skmv_kernel<KIND, 2, 2>;
-        case 3: return skmv_kernel<KIND, 3, 2>;
-        case 4: return skmv_kernel<KIND, 4, 2>;
-        case 5: return skmv_kernel<KIND, 5, 2>;
-        case 6: return skmv_kernel<KIND, 6, 2>;
-        case 7: return skmv_kernel<KIND, 7, 2>;
-        case 8: return skmv_kernel<KIND, 8, 2>;
-        case 9: return skmv_kernel<KIND, 9, 2>;
-        default: return skmv_kernel<KIND, 10, 2>;
+        case 1: return skmv_kernel<KIND, 1, 4, CW>;
+        case 2: return skmv_kernel<KIND, 2, 2, CW>;
+        case 3: return skmv_kernel<KIND, 3, 2, CW>;
+        case 4: return skmv_kernel<KIND, 4, 2, CW>;
+        case 5: return skmv_kernel<KIND, 5, 2, CW>;
+        case 6: return skmv_kernel<KIND, 6, 2, CW>;
+        case 7: return skmv_kernel<KIND, 7, 2, CW>;
+        case 8: return skmv_kernel<KIND, 8, 2, CW>;
+        case 9: return skmv_kernel<KIND, 9, 2, CW>;
+        default: return skmv_kernel<KIND, 10, 2, CW>;
     }
 }
+// Kernel for lt label tiles (0: kernel values) and cw blocks per wave.
+SplitFn split_fn(int kind, int lt, int cw) {
+    if (lt == 0) return kind == 0 ? skmv_kernel<0, 0, 4, 8> : skmv_kernel<1, 0, 4, 8>;
+    if (cw == 2) return kind == 0 ? fused_fn<0, 2>(lt) : fused_fn<1, 2>(lt);
+    if (cw == 4) return kind == 0 ? fused_fn<0, 4>(lt) : fused_fn<1, 4>(lt);
+    return kind == 0 ? fused_fn<0, 8>(lt) : fused_fn<1, 8>(lt);
+}
 
-// Queries per workgroup of the fused pass with lt label tiles.
-int split_rows(int64_t lt) { return lt <= 1 ? 256 : 128; }   // (0: kernel values)
+// Queries per workgroup: with one label tile the accumulators leave room for
+// four query blocks per wave, else for two.
+int split_rows(int64_t lt, int cw) { return (lt <= 1 ? 32 : 16) * cw; }
 
 int split_slots(SplitFn fn) {
     int dev = 0, cus = 256, per = 0;
@@ -656,8 +706,11 @@ hipError_t launch_pack_rows(PackArgs a, hipStream_t s) {
     a.panel = panel_bytes(a.P, a.d);
     const unsigned grid = (unsigned)(round_up(a.rows, a.P) / 16);
     const bool vec = a.d % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0;
-    if (vec) hipLaunchKernelGGL(pack_rows_kernel<true>, dim3(grid), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(pack_rows_kernel<false>, dim3(grid), dim3(256), 0, s, a);
+    // one wave per row where the workgroups alone do not fill the chip (a
+    // call of 64 rows of 440 features: 19 us with four waves)
+    const dim3 block(grid < 1024 ? 1024 : 256);
+    if (vec) hipLaunchKernelGGL(pack_rows_kernel<true>, dim3(grid), block, 0, s, a);
+    else hipLaunchKernelGGL(pack_rows_kernel<false>, dim3(grid), block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -670,11 +723,15 @@ hipError_t launch_pack_weights(const float* W, int64_t rows, int64_t l, int64_t 
 }
 
 SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, int max_slices) {
-    const SplitFn fn = kind == 0 ? fused_fn<0>((int)lt) : fused_fn<1>((int)lt);
-    const int64_t slots = split_slots(fn);
-    const int64_t tq = ceil_div(std::max<int64_t>(nq, 1), split_rows(lt));
+    // the fewest centre blocks per wave whose tile still holds all queries
+    int cw = 8;
+    if (lt > 0)
+        while (cw > 2 && split_rows(lt, cw / 2) >= nq) cw /= 2;
+    const int64_t slots = split_slots(split_fn(kind, (int)lt, cw));
+    const int64_t tq = ceil_div(std::max<int64_t>(nq, 1), split_rows(lt, cw));
     const int64_t nt = ceil_div(std::max<int64_t>(nc, 1), kCPanel);
     SplitPlan best{1, nt, 0.0};
+    best.cw = cw;
     double bt = 1e300;
     for (int64_t P = 1; P <= nt && P <= max_slices; ++P) {
         const int64_t per = ceil_div(nt, P);
@@ -727,9 +784,8 @@ hipError_t wmul_launch(WmulArgs a, const SplitPlan& p, hipStream_t s) {
 hipError_t split_launch(SplitArgs a, const SplitPlan& p, hipStream_t s) {
     a.tps = p.tps;
     sign_steps(a.nk, &a.neg0, &a.neg1);
-    const SplitFn fn = a.kind == 0 ? fused_fn<0>(a.lt) : fused_fn<1>(a.lt);
-    const int64_t tq = ceil_div(std::max<int64_t>(a.nq, 1), split_rows(a.lt));
-    hipLaunchKernelGGL(fn, dim3((unsigned)(tq * p.splits)), dim3(kSThreads), 0, s, a);
+    const int64_t tq = ceil_div(std::max<int64_t>(a.nq, 1), split_rows(a.lt, p.cw));
+    hipLaunchKernelGGL(split_fn(a.kind, a.lt, p.cw), dim3((unsigned)(tq * p.splits)), dim3(kSThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -113,6 +113,26 @@ def test_step_batch_edges(m, d, l):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("l", [3, 17, 160])
+@pytest.mark.parametrize("n_z", [1, 16, 31, 32, 33, 63, 64, 65, 127, 128, 129])
+def test_few_rows(l, n_z):
+    """Tiles of 32, 64 and 128 rows whose waves share the queries and split
+    the centres, and the reduction over many slices of few elements."""
+    n, d, bw = 128 * 300 + 5, 64, bw32(7.0)
+    rng = np.random.default_rng(n_z + l)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    Z = rng.standard_normal((n_z, d)).astype(np.float32)
+    a = rng.standard_normal((n, l)).astype(np.float32)
+    assert -(-n_z // 64) * 64 * n * d > 2 ** 27
+    with Gpu(X, l, "gaussian", bw, 20, 2, np.arange(20)) as g:
+        g.set_alpha(a)
+        P = g.predict(Z)
+    P_o = oracle.predict(X.astype(np.float64), a.astype(np.float64), Z.astype(np.float64),
+                         oracle.GAUSSIAN, bw)
+    assert np.max(np.abs(P - P_o) / _bound(X, Z, a, "gaussian", bw)) <= 1.0
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("l", [9, 300])
 @pytest.mark.parametrize("n_z", [3, 700])
 def test_noalloc_in_chunks(l, n_z):
