@@ -251,11 +251,12 @@ bool use_split(const ep_ctx* c, int64_t nq) {
 //    2^29 kernel entries (n = 1.28 M, d = 2048, l = 1000, m = 3561: 7.1e-5,
 //    6.0e-5, 7.5e-5; 203 against 90 ms; n = 256316, m = 2964: 7.3e-5 between
 //    the two). At n = 160000, m = 1601 the two are 2.3e-5 apart.
-bool use_split_step(const ep_ctx* c, int64_t m) {
-    return use_split(c, m) && !(c->kind == EP_LAPLACIAN && c->d > 2048) &&
-           !(c->lt16 > kMaxFusedTiles &&
-             (m > 2048 || (double)m * (double)c->n > (double)(1 << 29)));
+bool keeps_order(const ep_ctx* c, int64_t m) {
+    return (c->kind == EP_LAPLACIAN && c->d > 2048) ||
+           (c->lt16 > kMaxFusedTiles &&
+            (m > 2048 || (double)m * (double)c->n > (double)(1 << 29)));
 }
+bool use_split_step(const ep_ctx* c, int64_t m) { return use_split(c, m) && !keeps_order(c, m); }
 
 // Packs query rows for the split pass into `out`: rows idx[0 .. nq) of Z, or
 // its first nq rows. `training`: Z is X (rows 0 .. n - 1), whose norms and
@@ -851,12 +852,19 @@ int subsample_correction(ep_ctx* c, bool capture, const float* xb, const float* 
     const int64_t s = c->s, k = c->k, L = c->l_pad, kld = c->k_ld;
     const int64_t ldk = round_up(m, kBM);
     const int groups = 1024;
+    // Short products take chunks of one accumulation block (64): a tiny step
+    // (s = 500, m = 256) spends 41 us in them with chunks of 256, 17 us so.
+    // Where s m > 2^21 the products are long enough to fill the chip either
+    // way (15 us of 480 at s = 4000, m = 1310) and the chunks, which fix the
+    // order of summation, stay: the sums over the top eigenvector cancel, and
+    // their rounding is what a second step's result shows most.
+    const int64_t min_depth = keeps_order(c, m) || s * m > (int64_t(1) << 21) ? 256 : 64;
     const float* V = c->V.as<float>();
     // partial slices of one product into c->part, summed (and scaled) into out
     auto product = [&](const float* A, int64_t lda, bool a_t, const float* B, int64_t ldb,
                        int64_t M, int64_t N, int64_t K, const float* Dk, float* out,
                        int64_t ldo) -> int {
-        const ThinGemmPlan pl = thin_gemm_plan(M, N, K, groups);
+        const ThinGemmPlan pl = thin_gemm_plan(M, N, K, groups, min_depth);
         const int64_t slice = M * ldo;
         const bool direct = pl.chunks == 1 && !Dk;
         if (!direct) HIP_TRY(c->part.ensure((size_t)pl.chunks * slice * sizeof(float)));

@@ -229,8 +229,8 @@ struct ThinGemmPlan {
     int64_t tiles = 0;
 };
 // Depth chunks so that tiles x chunks reaches min_groups workgroups (each
-// chunk at least 256 deep, at most 64 chunks).
-ThinGemmPlan thin_gemm_plan(int64_t M, int64_t N, int64_t K, int min_groups);
+// chunk at least min_depth deep, at most 64 chunks).
+ThinGemmPlan thin_gemm_plan(int64_t M, int64_t N, int64_t K, int min_groups, int64_t min_depth);
 hipError_t thin_gemm_launch(const ThinGemmArgs& a, const ThinGemmPlan& pl, bool a_t, bool scatter,
                             hipStream_t st);
 // out[i, j] = Dk[i] * sum_p part[p slice + i ld + j] (no scale when Dk is

@@ -44,15 +44,16 @@ constexpr int kBlk = 64;              // depth per accumulation block
 constexpr int kGThreads = 256;
 constexpr int kPadA = 4, kPadB = 4;   // LDS row padding (floats)
 
-// Loads floats [j0, j0 + 4) of a row of `len` valid floats: one 16-byte load
-// when all four are in range (rows 16-byte aligned), else element by element.
-__device__ __forceinline__ float4 ld4(const float* row, int64_t j0, int64_t len) {
-    if (j0 + 4 <= len) return *reinterpret_cast<const float4*>(row + j0);
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (j0 < len) v.x = row[j0];
-    if (j0 + 1 < len) v.y = row[j0 + 1];
-    if (j0 + 2 < len) v.z = row[j0 + 2];
-    if (j0 + 3 < len) v.w = row[j0 + 3];
+// The first `len` (of four) floats at `at`, zero after them; nothing at `at`
+// is read when len <= 0 (the load then goes to `safe`). No branch: a load
+// inside one is waited for where the paths join, and the four loads of a
+// stage would each cost their latency.
+__device__ __forceinline__ float4 ld4(const float* at, int64_t len, const float* safe) {
+    float4 v = *reinterpret_cast<const float4*>(len > 0 ? at : safe);
+    v.x = len > 0 ? v.x : 0.f;
+    v.y = len > 1 ? v.y : 0.f;
+    v.z = len > 2 ? v.z : 0.f;
+    v.w = len > 3 ? v.w : 0.f;
     return v;
 }
 
@@ -88,19 +89,17 @@ __global__ void __launch_bounds__(kGThreads) thin_gemm_kernel(ThinGemmArgs p) {
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int q = tid + e * kGThreads;
-            ra[e] = make_float4(0.f, 0.f, 0.f, 0.f);
             if (A_T) {
                 // A(i, kk) = A[kk * lda + i]: quad of (depth, 4 rows)
                 const int kk = q / (kTM / 4), ii = 4 * (q % (kTM / 4));
-                if (kk < kd) ra[e] = ld4(p.A + (k0 + kk) * p.lda + i0, ii, p.M - i0);
+                ra[e] = ld4(p.A + (k0 + kk) * p.lda + i0 + ii, kk < kd ? p.M - i0 - ii : 0, p.A);
             } else {
                 // A(i, kk) = A[i * lda + kk]: quad of (row, 4 depth)
                 const int ii = q / (kKS / 4), kk = 4 * (q % (kKS / 4));
-                if (i0 + ii < p.M) ra[e] = ld4(p.A + (i0 + ii) * p.lda + k0, kk, kd);
+                ra[e] = ld4(p.A + (i0 + ii) * p.lda + k0 + kk, i0 + ii < p.M ? kd - kk : 0, p.A);
             }
             const int kk = q / (kTN / 4), jj = 4 * (q % (kTN / 4));
-            rb[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (kk < kd) rb[e] = ld4(p.B + (k0 + kk) * p.ldb + j0, jj, p.N - j0);
+            rb[e] = ld4(p.B + (k0 + kk) * p.ldb + j0 + jj, kk < kd ? p.N - j0 - jj : 0, p.B);
         }
     };
     // A tile -> As[depth][row], B tile -> Bs[depth][col]
@@ -153,14 +152,21 @@ __global__ void __launch_bounds__(kGThreads) thin_gemm_kernel(ThinGemmArgs p) {
     const int64_t col = j0 + wn * 32 + (lane & 31);
     if (SCATTER) {
         if (col >= p.N_valid) return;
+        // all rows and old values first: a store between two loads would
+        // order them, and each update would cost its own round trip
+        int64_t r[16];
+        float old[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            r[v] = p.r[min(i0 + wm * 32 + acc_row(v, lane), p.M - 1)];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) old[v] = p.alpha[r[v] * p.ldalpha + col];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const int64_t row = i0 + wm * 32 + acc_row(v, lane);
-            if (row < p.M) {
-                const int64_t r = p.r[row];
-                const float a = p.alpha[r * p.ldalpha + col] + p.coef * sum[v];
-                p.alpha[r * p.ldalpha + col] = a;
-                if (p.planes) store_weight(p.planes, weight_elem(r, col, p.lt), a);
+            if (i0 + wm * 32 + acc_row(v, lane) < p.M) {
+                const float a = old[v] + p.coef * sum[v];
+                p.alpha[r[v] * p.ldalpha + col] = a;
+                if (p.planes) store_weight(p.planes, weight_elem(r[v], col, p.lt), a);
             }
         }
     } else {
@@ -183,20 +189,31 @@ __global__ void __launch_bounds__(256) sum_slices_kernel(const float* part, int 
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= rows * cols) return;
     const int64_t i = e / cols, j = e - i * cols;
+    const float* at = part + i * ld + j;
     float f = 0.f;
-    for (int s = 0; s < slices; ++s) f += part[(int64_t)s * slice + i * ld + j];
+    int s = 0;
+    for (; s + 8 <= slices; s += 8) {           // eight loads in flight
+        float v[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[x] = at[(int64_t)(s + x) * slice];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) f += v[x];
+    }
+    for (; s < slices; ++s) f += at[(int64_t)s * slice];
     out[i * ldo + j] = Dk ? Dk[i] * f : f;
 }
 
 }  // namespace
 
-ThinGemmPlan thin_gemm_plan(int64_t M, int64_t N, int64_t K, int min_groups) {
+ThinGemmPlan thin_gemm_plan(int64_t M, int64_t N, int64_t K, int min_groups, int64_t min_depth) {
     ThinGemmPlan pl;
     const int64_t tiles = ceil_div(M, kTM) * ceil_div(N, kTN);
     // depth chunks: enough workgroups to fill the chip, chunks of whole
-    // accumulation blocks and at least 256 deep
+    // accumulation blocks and at least min_depth deep. A stage of 32 costs a
+    // workgroup about 1.6 us however few of them run, so short products want
+    // chunks of one block (20 x 256 x 500: 26 us in one chunk, 7 in eight).
     int64_t chunks = std::max<int64_t>(1, ceil_div(min_groups, tiles));
-    chunks = std::min<int64_t>(chunks, std::max<int64_t>(1, K / 256));
+    chunks = std::min<int64_t>(chunks, std::max<int64_t>(1, K / min_depth));
     chunks = std::min<int64_t>(chunks, 64);
     pl.kc = round_up(ceil_div(K, chunks), kBlk);
     pl.chunks = (int)ceil_div(K, pl.kc);

@@ -154,3 +154,24 @@ def test_noalloc_in_chunks(l, n_z):
     P_o = oracle.predict(X.astype(np.float64), a.astype(np.float64), Z.astype(np.float64),
                          oracle.GAUSSIAN, bw)
     assert np.max(np.abs(P - P_o) / _bound(X, Z, a, "gaussian", bw)) <= 1.0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("s,m,k,l", [(63, 64, 1, 3), (64, 65, 20, 4), (65, 129, 21, 70),
+                                     (500, 256, 63, 5), (1000, 300, 64, 33), (257, 4100, 65, 9)])
+def test_correction_chunks(s, m, k, l):
+    """Steps 4-5 in chunks of one accumulation block (s m <= 2^21), ragged in
+    every dimension: alpha after one step."""
+    n, d, bw = 4300, 20, bw32(1.1)
+    rng = np.random.default_rng(s + m)
+    X = (rng.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    Y = np.eye(l, dtype=np.float32)[rng.integers(0, l, n)]
+    a0 = (rng.standard_normal((n, l)) / np.sqrt(n)).astype(np.float32)
+    r = rng.choice(n, s, replace=False)
+    t = rng.choice(n, m, replace=False)
+    st = oracle.setup(X, oracle.GAUSSIAN, bw, s, min(k, s - 1), r)
+    a_o, _ = oracle.step(st, a0, t, Y[t])
+    with Gpu(X, l, "gaussian", bw, s, min(k, s - 1), r) as g:
+        g.set_alpha(a0)
+        g.step(t, Y[t])
+        assert rel(g.alpha() - a0, a_o - a0) < TOL_STEP
