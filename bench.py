@@ -28,6 +28,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3     # MI355X dense fp32 matrix peak
+PEAK_16BIT_MFMA_TFLOPS = 2500.0   # MI355X dense fp16 / bf16 matrix peak
 PEAK_HBM_GBS = 8000.0
 
 
@@ -36,7 +37,19 @@ def log(msg):
 
 
 KERNEL_SOURCES = {"kmv_kernel": ["kmv.hip", "ep_device.h"],
+                  "skmv_kernel": ["skmv.hip", "split.h", "ep_device.h"],
                   "kblock_kernel": ["kblock.hip", "ep_device.h"]}
+
+
+def split_step(n, d, l, kernel, m):
+    """Whether a fused training step runs on the 16-bit matrix cores (the
+    library's use_split_step, where its packed operands fit the device)."""
+    tiles = -(-l // 16)
+    if kernel == "laplacian" and d > 2048:
+        return False
+    if tiles > 10 and (m > 2048 or m * n > 1 << 29):
+        return False
+    return -(-m // 64) * 64 * n * d > 1 << 27
 
 
 def code_text(src):
@@ -490,7 +503,8 @@ def traffic_summary(fetch_csv, write_csv, workload, kernel, n_step, command_note
                 if row["Counter_Name"] != counter:
                     continue
                 name = row["Kernel_Name"]
-                key = ("kmv_kernel" if "kmv_kernel<" in name else
+                key = ("skmv_kernel" if "skmv_kernel<" in name else
+                       "kmv_kernel" if "kmv_kernel<" in name else
                        "kmv_subsample_kernel" if "kmv_subsample_kernel<" in name else
                        "kblock_kernel" if "kblock_kernel<" in name else
                        "copy" if "copyBuffer" in name and float(row["Counter_Value"]) > (1 << 18) else
@@ -743,6 +757,7 @@ def main():
     # recomputes them in a subsample pass (distances and product)
     sub_flops = 2.0 * m * s * (d + l) if blocked else 2.0 * m * s * l
     step_flops = kmv_flops + sub_flops + 4.0 * s * k * l
+    peak = PEAK_FP32_MFMA_TFLOPS
     if blocked:
         # dominant kernel: the kernel block (distances -> kernel values);
         # its algorithmic work is 2 d flops per entry, over all chunks
@@ -759,6 +774,12 @@ def main():
         dom_avg_s = kmv_avg_s
         dom_flops = kmv_flops
         gemm_tflops = None
+        if args.contraction != "blocked" and split_step(n, d, l, cfg.kernel, m):
+            # three fp16 products per feature, six bf16 products per label
+            dom = "skmv_kernel"
+            dom_label = "skmv_kernel (step 2 on the 16-bit matrix cores: 3 d + 6 l products per entry)"
+            dom_flops = 2.0 * m * n * (3 * d + 6 * l)
+            peak = PEAK_16BIT_MFMA_TFLOPS
     achieved = dom_flops / dom_avg_s / 1e12
     workload = f"{cfg.name}-shaped n={n} d={d} l={l} {cfg.kernel} bw={cfg.bandwidth:g} s={s} k={k} m={m}"
     if args.shard > 1:
@@ -812,9 +833,9 @@ def main():
         "roofline": {
             "bound": "mfma",
             "achieved": achieved,
-            "peak": PEAK_FP32_MFMA_TFLOPS,
+            "peak": peak,
             "unit": "TFLOP/s",
-            "frac": achieved / PEAK_FP32_MFMA_TFLOPS,
+            "frac": achieved / peak,
             "traffic": traffic,
             "traffic_source": traffic_prov,
             "kernel": dom_label,
@@ -823,7 +844,7 @@ def main():
             "flops_per_launch": dom_flops,
             "probe_mfma_f32_tflops": probe_tf,
             "probe_shader_clock_mhz": probe_mhz,
-            "frac_of_probe": achieved / probe_tf if probe_tf > 0 else None,
+            "frac_of_probe": achieved / probe_tf if probe_tf > 0 and dom != "skmv_kernel" else None,
         },
         "cpu_baseline": cpu,
         "predict": predict,

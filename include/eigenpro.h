@@ -177,8 +177,9 @@ int ep_restore(ep_ctx** ctx, const float* X, int64_t n, int64_t d, int64_t l,
  * sigma_i. K(X_r, X_t) is not recomputed: the fused step-2 pass keeps
  * those columns of the kernel block (a context buffer of s x m floats, at
  * most 2 GiB, grown on demand) as the paper reads them from its stored
- * block; past that size, with the blocked form, or for rows that are not
- * 16-byte aligned, a separate fused pass recomputes them.
+ * block; past that size, with the blocked form, or where the float32 pass
+ * meets rows that are not 16-byte aligned, a separate fused pass recomputes
+ * them.
  * Asynchronous. Indices outside [0, n) are not read or written
  * and make the next ep_sync return EP_EINDEX; repeated indices are
  * rejected with EP_EINDEX only when index checking is enabled
@@ -309,7 +310,9 @@ int ep_timing_read(ep_ctx* ctx, ep_timing* out);
  *                        (at most block_bytes), then a GEMM adds block x
  *                        alpha chunk into F. Needs d % 4 == 0 and 16-byte aligned
  *                        rows (else the fused form runs).
- *   EP_CONTRACT_AUTO     the fused form (default). The blocked form is
+ *   EP_CONTRACT_AUTO     the fused form (default); beyond 160 labels a chunk
+ *                        of kernel values may be stored (at most 4 GiB) and
+ *                        contracted by a second kernel. The blocked form is
  *                        slower (a little at l = 1000, several times at
  *                        small l, where its GEMM is skinny) and writes the
  *                        block to memory, so it is only taken on request.

@@ -291,6 +291,12 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
             for (int i = 0; i < QB; ++i) sacc[c][i] = mfma_f16(ah, b[i][0], sacc[c][i]);
             __builtin_amdgcn_sched_barrier(0);
         }
+        // Stage ks + 1 is in LDS for everyone after this barrier without a
+        // wait of its own: the products above waited for this step's queries,
+        // whose load was issued after dma(ks + 1) (in step ks - 1, which
+        // issued dma(ks + 2) after it), and vector-memory operations of a
+        // wave complete in order. The scheduling barriers keep the products
+        // on this side.
         wg_barrier<-1>();
     };
 
