@@ -25,6 +25,7 @@
 // The large products (K times the block, projections, rotations) are
 // float64 GEMMs; the p x p Ritz problem and the QR use rocSOLVER.
 #include "eigenpro.h"
+#include "ep_device.h"
 #include "ep_host.h"
 #include "ep_internal.h"
 
@@ -101,6 +102,104 @@ __global__ void __launch_bounds__(256) reverse_pairs_kernel(const double* W, con
     if (threadIdx.x == 0) wr[j] = w[p - 1 - j];
 }
 
+// out (s x cols) = K Y for the symmetric K (s x s) and Y (s x cols), all
+// column-major float64: the products of the filter. One workgroup of 8 waves
+// owns 64 x 64 of the result, a wave 32 x 16 as two blocks of
+// v_mfma_f64_16x16x4f64; stages of 32 depth pass through two LDS buffers,
+// loaded into registers two stages ahead (a stage's products are shorter than
+// a load from memory). The column tiles
+// of a block row share its part of K, so they run on one XCD (workgroups go
+// to the 8 XCDs round robin). No load needs more than 8-byte alignment: s may
+// be odd.
+constexpr int kET = 64, kEK = 32, kEThreads = 512;
+
+__global__ void __launch_bounds__(kEThreads) symm_product_kernel(const double* K, const double* Y,
+                                                                 int64_t s, int64_t cols,
+                                                                 double* out) {
+    typedef double doublex4 __attribute__((ext_vector_type(4)));
+    __shared__ double As[2][kEK][kET + 16], Bs[2][kET][kEK + 2];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g = lane >> 4;
+    const int ny = (int)((cols + kET - 1) / kET);
+    const int at = (int)blockIdx.x >> 3;
+    const int64_t i0 = ((int64_t)(at / ny) * 8 + (blockIdx.x & 7)) * kET;
+    const int64_t j0 = (int64_t)(at % ny) * kET;
+    if (i0 >= s) return;
+    const int wi = (wave & 1) * 32, wj = (wave >> 1) * 16;
+    // rows and columns past the end repeat the last one and are not stored;
+    // depth past the end repeats the last one and is zero in LDS
+    const double* a0 = K + min(i0 + lane, s - 1);
+    const int kb = tid & 31;
+    const double* b0[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b0[e] = Y + min(j0 + (tid >> 5) + 16 * e, cols - 1) * s;
+    double ra0[4], rb0[4], ra1[4], rb1[4];
+    auto load = [&](double (&ra)[4], double (&rb)[4], int64_t k0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            ra[e] = a0[min(k0 + wave + 8 * e, s - 1) * s];
+            rb[e] = b0[e][min(k0 + kb, s - 1)];
+        }
+    };
+    auto put = [&](int buf, const double (&ra)[4], const double (&rb)[4], int64_t k0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            As[buf][wave + 8 * e][lane] = k0 + wave + 8 * e < s ? ra[e] : 0.0;
+            Bs[buf][(tid >> 5) + 16 * e][kb] = k0 + kb < s ? rb[e] : 0.0;
+        }
+    };
+    doublex4 acc[2] = {doublex4{0.0, 0.0, 0.0, 0.0}, doublex4{0.0, 0.0, 0.0, 0.0}};
+    // one stage: its products from LDS buffer `buf`, the next stage (loaded
+    // a stage ago) into the other buffer, the one after next on its way
+    auto stage = [&](int buf, double (&ra)[4], double (&rb)[4], const double (&na)[4],
+                     const double (&nb)[4], int64_t k0) {
+        load(ra, rb, k0 + 2 * kEK);
+        __builtin_amdgcn_sched_barrier(0);
+        // (each stage is summed from zero: a chain of s terms loses more)
+        doublex4 t[2] = {doublex4{0.0, 0.0, 0.0, 0.0}, doublex4{0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+        for (int kk = 0; kk < kEK; kk += 4) {
+            const double b = Bs[buf][wj + r16][kk + g];
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+                t[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(As[buf][kk + g][wi + 16 * x + r16], b,
+                                                            t[x], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) acc[x] += t[x];
+        // (the other buffer was last read before the previous barrier)
+        put(buf ^ 1, na, nb, k0 + kEK);
+        wg_barrier<-1>();
+    };
+    load(ra0, rb0, 0);
+    load(ra1, rb1, kEK);
+    put(0, ra0, rb0, 0);
+    wg_barrier<-1>();
+    for (int64_t k0 = 0; k0 < s; k0 += 2 * kEK) {
+        stage(0, ra0, rb0, ra1, rb1, k0);
+        if (k0 + kEK < s) stage(1, ra1, rb1, ra0, rb0, k0 + kEK);
+    }
+    // element v of a block: row 4 v + lane / 16, column lane % 16
+    const int64_t j = j0 + wj + r16;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t i = i0 + wi + 16 * x + 4 * v + g;
+            if (i < s && j < cols) out[j * s + i] = acc[x][v];
+        }
+}
+
+hipError_t launch_symm_product(const double* K, const double* Y, int64_t s, int64_t cols,
+                               double* out, hipStream_t st) {
+    const int64_t grid = round_up(ceil_div(s, kET), 8) * ceil_div(cols, kET);
+    hipLaunchKernelGGL(symm_product_kernel, dim3((unsigned)grid), dim3(kEThreads), 0, st, K, Y, s,
+                       cols, out);
+    return hipGetLastError();
+}
+
 inline unsigned nblocks(int64_t count) { return (unsigned)((count + 255) / 256); }
 
 struct Blas {
@@ -169,6 +268,15 @@ int subspace_topq(const double* K, int64_t s, int64_t q, const EigOpts& o, uint6
 
     auto product = [&](const double* Y, int64_t cols, double* out) {
         matvecs += cols;
+        // Between these sizes the library's tiles leave most of the chip idle
+        // over one long chain of depth; below it splits the depth, above its
+        // larger tiles win. 208 columns, own against library kernel: s = 3200
+        // 0.16 / 0.10 ms (140 columns), 4000 0.20 / 0.44, 6000 0.49 / 0.66,
+        // 8000 0.64 / 0.87, 12000 1.46 / 1.31.
+        if (s > 3584 && s <= 10240) {
+            HIP_TRY(launch_symm_product(K, Y, s, cols, out, st));
+            return (int)EP_OK;
+        }
         return blas.gemm(false, false, s, cols, s, 1.0, K, s, Y, s, 0.0, out, s);
     };
     // Y -= V_L (V_L^T Y)

@@ -140,3 +140,19 @@ def test_subspace_full_size_setup(name):
     sigma, V = sub[1], sub[3].astype(np.float64)
     res = Ks @ V - V * sigma[:cfg.k]
     assert np.linalg.norm(res) / np.linalg.norm(Ks) < 1e-6
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("s,k", [(3585, 37), (3648, 10), (3711, 3)])
+def test_subspace_product_edges(s, k):
+    """The filter's own product (3584 < s <= 10240): one row and one depth
+    past the tiles, exact tiles, one short of them; ragged column counts, and
+    rows of V whose rank is no multiple of four."""
+    cfg = synth.get_config("mnist", n=4500, s=s, k=k)
+    X = synth.features(cfg, 0)
+    r = synth.subsample_indices(cfg, 0)
+    sub = _setup(X, cfg, r, solver="subspace", no_fallback=1)
+    den = _setup(X, cfg, r, solver="dense")
+    assert sub[0].solver == SUBSPACE and sub[0].eig_residual <= 1e-11
+    _agree(sub, den)
