@@ -3,6 +3,7 @@
 // batch-block update (Algorithm 1 step 3), and the float64 subsample kernel
 // matrix of the initialisation.
 #include "ep_internal.h"
+#include "launch.h"
 #include "split.h"
 
 #include <math.h>
@@ -208,8 +209,9 @@ __global__ void __launch_bounds__(256) extract_eigvecs_kernel(const double* Z, i
 }
 
 __global__ void __launch_bounds__(256) fill_kernel(float* p, int64_t count, float v) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < count) p[e] = v;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < count;
+         e += (int64_t)gridDim.x * 256)
+        p[e] = v;
 }
 
 // Up to this many elements (one per resident thread or fewer) the reductions
@@ -285,7 +287,8 @@ hipError_t launch_extract_eigvecs(const double* Z, int64_t ldz, int64_t col0, in
 
 hipError_t launch_fill_f32(float* p, int64_t count, float v, hipStream_t st) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(fill_kernel, dim3(blocks_for(count)), dim3(256), 0, st, p, count, v);
+    hipLaunchKernelGGL(fill_kernel, dim3(stride_grid(ceil_div(count, 256), 256)), dim3(256), 0, st, p,
+                       count, v);
     return hipGetLastError();
 }
 

@@ -27,6 +27,7 @@
 // 6.6 at 144 labels.
 #include "ep_device.h"
 #include "ep_internal.h"
+#include "launch.h"
 #include "split.h"
 
 #include <algorithm>
@@ -50,98 +51,101 @@ __global__ void __launch_bounds__(1024) pack_rows_kernel(PackArgs p) {
     __shared__ float s_norm[16], s_inv[16], s_scale[16];
     __shared__ int64_t s_row[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
-    const int64_t tile = blockIdx.x;
-    if (tid < 16) {
-        const int64_t b = tile * 16 + tid;
-        int64_t src = b < p.rows ? b : -1;
-        if (p.idx && src >= 0) {
-            src = p.idx[b];
-            if (src < 0 || src >= p.n) {
-                atomicOr(p.err, 1);
-                src = -1;
-            }
-        }
-        s_row[tid] = src;
-        if (p.norms_in) {
-            s_norm[tid] = src >= 0 ? p.norms_in[src] : 0.f;
-            s_inv[tid] = src >= 0 ? p.inv_in[src] : 1.f;
-        }
-    }
-    __syncthreads();
-    if (!p.norms_in) {
-        for (int r = wave; r < 16; r += waves) {
-            const int64_t src = s_row[r];
-            double acc = 0.0;
-            float mx = 0.f;
-            if (src >= 0) {
-                const float* x = p.X + src * p.d;
-                for (int64_t j = lane; j < p.d; j += 64) {
-                    const float f = x[j];
-                    const double v = f;
-                    acc += v * v;
-                    mx = fmaxf(mx, fabsf(f));
+    const int64_t tiles = (p.rows + p.P - 1) / p.P * (p.P / 16);
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        if (tid < 16) {
+            const int64_t b = tile * 16 + tid;
+            int64_t src = b < p.rows ? b : -1;
+            if (p.idx && src >= 0) {
+                src = p.idx[b];
+                if (src < 0 || src >= p.n) {
+                    atomicOr(p.err, 1);
+                    src = -1;
                 }
             }
-            for (int off = 32; off > 0; off >>= 1) {
-                acc += __shfl_down(acc, off, 64);
-                mx = fmaxf(mx, __shfl_down(mx, off, 64));
-            }
-            if (lane == 0) {
-                // largest element into [2^14, 2^15); exponents below -63
-                // (squares below the float32 range) share one scale
-                const int e = mx == 0.f ? 14
-                                        : min(127, max(-63, (int)(__builtin_bit_cast(unsigned, mx) >> 23) - 127));
-                s_norm[r] = (float)acc;
-                s_inv[r] = __builtin_bit_cast(float, (unsigned)(e - 14 + 127) << 23);
+            s_row[tid] = src;
+            if (p.norms_in) {
+                s_norm[tid] = src >= 0 ? p.norms_in[src] : 0.f;
+                s_inv[tid] = src >= 0 ? p.inv_in[src] : 1.f;
             }
         }
         __syncthreads();
-    }
-    if (tid < 16) {
-        // a power of two: its reciprocal is exact
-        s_scale[tid] = 1.f / s_inv[tid];
-        const int64_t b = tile * 16 + tid;
-        const int64_t panel = b / p.P, at = b % p.P;
-        float* meta = reinterpret_cast<float*>(p.out + panel * p.panel + p.nk * (p.P / 16) * 2 * kFragBytes);
-        meta[at] = s_norm[tid];
-        meta[p.P + at] = s_inv[tid];
-        if (b < p.rows) {
-            if (p.norms_out) p.norms_out[b] = s_norm[tid];
-            if (p.inv_out) p.inv_out[b] = s_inv[tid];
+        if (!p.norms_in) {
+            for (int r = wave; r < 16; r += waves) {
+                const int64_t src = s_row[r];
+                double acc = 0.0;
+                float mx = 0.f;
+                if (src >= 0) {
+                    const float* x = p.X + src * p.d;
+                    for (int64_t j = lane; j < p.d; j += 64) {
+                        const float f = x[j];
+                        const double v = f;
+                        acc += v * v;
+                        mx = fmaxf(mx, fabsf(f));
+                    }
+                }
+                for (int off = 32; off > 0; off >>= 1) {
+                    acc += __shfl_down(acc, off, 64);
+                    mx = fmaxf(mx, __shfl_down(mx, off, 64));
+                }
+                if (lane == 0) {
+                    // largest element into [2^14, 2^15); exponents below -63
+                    // (squares below the float32 range) share one scale
+                    const int e = mx == 0.f ? 14
+                                            : min(127, max(-63, (int)(__builtin_bit_cast(unsigned, mx) >> 23) - 127));
+                    s_norm[r] = (float)acc;
+                    s_inv[r] = __builtin_bit_cast(float, (unsigned)(e - 14 + 127) << 23);
+                }
+            }
+            __syncthreads();
         }
-    }
-    __syncthreads();
-    const int row = lane & 15, g = lane >> 4;
-    const int64_t src = s_row[row];
-    const float sc = s_scale[row];
-    const float* x = p.X + (src >= 0 ? src : 0) * p.d;
-    const int64_t t_panel = p.P / 16;
-    char* out = p.out + (tile / t_panel) * p.panel + (tile % t_panel) * 2 * kFragBytes + lane * 16;
-    for (int64_t ks = wave; ks < p.nk; ks += waves) {
-        const int64_t c0 = ks * 32 + 8 * g;
-        const float sck = ks >= p.neg0 && ks < p.neg1 ? -sc : sc;
-        float v[8];
-        if (VEC) {
-            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-            const float4 a = src >= 0 && c0 < p.d ? *reinterpret_cast<const float4*>(x + c0) : z;
-            const float4 b = src >= 0 && c0 + 4 < p.d ? *reinterpret_cast<const float4*>(x + c0 + 4) : z;
-            v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-            v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-        } else {
+        if (tid < 16) {
+            // a power of two: its reciprocal is exact
+            s_scale[tid] = 1.f / s_inv[tid];
+            const int64_t b = tile * 16 + tid;
+            const int64_t panel = b / p.P, at = b % p.P;
+            float* meta = reinterpret_cast<float*>(p.out + panel * p.panel + p.nk * (p.P / 16) * 2 * kFragBytes);
+            meta[at] = s_norm[tid];
+            meta[p.P + at] = s_inv[tid];
+            if (b < p.rows) {
+                if (p.norms_out) p.norms_out[b] = s_norm[tid];
+                if (p.inv_out) p.inv_out[b] = s_inv[tid];
+            }
+        }
+        __syncthreads();
+        const int row = lane & 15, g = lane >> 4;
+        const int64_t src = s_row[row];
+        const float sc = s_scale[row];
+        const float* x = p.X + (src >= 0 ? src : 0) * p.d;
+        const int64_t t_panel = p.P / 16;
+        char* out = p.out + (tile / t_panel) * p.panel + (tile % t_panel) * 2 * kFragBytes + lane * 16;
+        for (int64_t ks = wave; ks < p.nk; ks += waves) {
+            const int64_t c0 = ks * 32 + 8 * g;
+            const float sck = ks >= p.neg0 && ks < p.neg1 ? -sc : sc;
+            float v[8];
+            if (VEC) {
+                const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+                const float4 a = src >= 0 && c0 < p.d ? *reinterpret_cast<const float4*>(x + c0) : z;
+                const float4 b = src >= 0 && c0 + 4 < p.d ? *reinterpret_cast<const float4*>(x + c0 + 4) : z;
+                v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+                v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+            } else {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = src >= 0 && c0 + j < p.d ? x[c0 + j] : 0.f;
-        }
-        half8 hi, lo;
+                for (int j = 0; j < 8; ++j) v[j] = src >= 0 && c0 + j < p.d ? x[c0 + j] : 0.f;
+            }
+            half8 hi, lo;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float s = v[j] * sck;
-            const _Float16 h = (_Float16)s;
-            hi[j] = h;
-            lo[j] = __builtin_isfinite(s) ? (_Float16)(s - (float)h) : (_Float16)0.f;
+            for (int j = 0; j < 8; ++j) {
+                const float s = v[j] * sck;
+                const _Float16 h = (_Float16)s;
+                hi[j] = h;
+                lo[j] = __builtin_isfinite(s) ? (_Float16)(s - (float)h) : (_Float16)0.f;
+            }
+            char* o = out + ks * t_panel * 2 * kFragBytes;
+            *reinterpret_cast<half8*>(o) = hi;
+            *reinterpret_cast<half8*>(o + kFragBytes) = lo;
         }
-        char* o = out + ks * t_panel * 2 * kFragBytes;
-        *reinterpret_cast<half8*>(o) = hi;
-        *reinterpret_cast<half8*>(o + kFragBytes) = lo;
+        __syncthreads();               // the next tile overwrites the rows and scales
     }
 }
 
@@ -149,10 +153,11 @@ __global__ void __launch_bounds__(1024) pack_rows_kernel(PackArgs p) {
 __global__ void __launch_bounds__(256) pack_weights_kernel(const float* W, int64_t rows, int64_t l,
                                                            int64_t ldw, int64_t lt,
                                                            unsigned short* planes) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= rows * l) return;
-    const int64_t c = e / l, j = e - c * l;
-    store_weight(planes, weight_elem(c, j, lt), W[c * ldw + j]);
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < rows * l;
+         e += (int64_t)gridDim.x * 256) {
+        const int64_t c = e / l, j = e - c * l;
+        store_weight(planes, weight_elem(c, j, lt), W[c * ldw + j]);
+    }
 }
 
 // ---- the fused pass --------------------------------------------------------
@@ -710,21 +715,22 @@ hipError_t launch_pack_rows(PackArgs a, hipStream_t s) {
     a.neg0 = a.neg1 = -1;
     if (a.queries) sign_steps(a.nk, &a.neg0, &a.neg1);
     a.panel = panel_bytes(a.P, a.d);
-    const unsigned grid = (unsigned)(round_up(a.rows, a.P) / 16);
+    const int64_t tiles = round_up(a.rows, a.P) / 16;
     const bool vec = a.d % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0;
     // one wave per row where the workgroups alone do not fill the chip (a
     // call of 64 rows of 440 features: 19 us with four waves)
-    const dim3 block(grid < 1024 ? 1024 : 256);
-    if (vec) hipLaunchKernelGGL(pack_rows_kernel<true>, dim3(grid), block, 0, s, a);
-    else hipLaunchKernelGGL(pack_rows_kernel<false>, dim3(grid), block, 0, s, a);
+    const dim3 block(tiles < 1024 ? 1024 : 256);
+    const dim3 grid(stride_grid(tiles, (int)block.x));
+    if (vec) hipLaunchKernelGGL(pack_rows_kernel<true>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(pack_rows_kernel<false>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_pack_weights(const float* W, int64_t rows, int64_t l, int64_t ldw, int64_t lt,
                                void* planes, hipStream_t s) {
     if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(pack_weights_kernel, dim3((unsigned)ceil_div(rows * l, 256)), dim3(256), 0, s,
-                       W, rows, l, ldw, lt, static_cast<unsigned short*>(planes));
+    hipLaunchKernelGGL(pack_weights_kernel, dim3(stride_grid(ceil_div(rows * l, 256), 256)), dim3(256),
+                       0, s, W, rows, l, ldw, lt, static_cast<unsigned short*>(planes));
     return hipGetLastError();
 }
 
