@@ -110,11 +110,13 @@ struct ep_ctx {
     DevBuf kpos;                        // n ints: subsample position of each row, or -1
     DevBuf ksb;                         // s x round_up(m, 64): K(X_r, X_t) captured in step 2
     // split-precision operands (split.h), held while `split` is set: the
-    // packed centres, their inverse scales, and the planes of alpha (lt16
-    // label tiles of 16)
+    // packed centres, their inverse scales, the panels whose low planes are
+    // multiplied with each other too, and the planes of alpha (lt16 label
+    // tiles of 16)
     bool split = false;
+    bool any_lolo = false;              // some panel's are
     int64_t lt16 = 0;
-    DevBuf Xp, xinv, wplanes;
+    DevBuf Xp, xinv, lolo, wplanes;
     // per-call scratch
     DevBuf xb, xb_norms, R, part, G, vt_part, W1, zn, Qp;
 
@@ -129,8 +131,8 @@ struct ep_ctx {
 
     ~ep_ctx() {
         for (DevBuf* b : {&norms, &alpha, &r_dev, &Xs, &xs_norms, &V, &Dk, &err, &kpos, &ksb,
-                          &xb, &xb_norms, &R, &part, &G, &vt_part, &W1, &zn, &Xp, &xinv, &wplanes,
-                          &Qp})
+                          &xb, &xb_norms, &R, &part, &G, &vt_part, &W1, &zn, &Xp, &xinv, &lolo,
+                          &wplanes, &Qp})
             b->release();
         for (auto& p : kmv_ev) {
             (void)hipEventDestroy(p.a);
@@ -259,8 +261,8 @@ bool keeps_order(const ep_ctx* c, int64_t m) {
 bool use_split_step(const ep_ctx* c, int64_t m) { return use_split(c, m) && !keeps_order(c, m); }
 
 // Packs query rows for the split pass into `out`: rows idx[0 .. nq) of Z, or
-// its first nq rows. `training`: Z is X (rows 0 .. n - 1), whose norms and
-// scales are held.
+// its first nq rows. `training`: Z is X (rows 0 .. n - 1), whose scales are
+// held.
 int pack_queries(ep_ctx* c, const float* Z, const int64_t* idx, int64_t nq, char* out,
                  bool training) {
     PackArgs a{};
@@ -269,10 +271,7 @@ int pack_queries(ep_ctx* c, const float* Z, const int64_t* idx, int64_t nq, char
     a.d = c->d;
     a.idx = idx;
     a.rows = nq;
-    if (training) {
-        a.norms_in = c->norms.as<float>();
-        a.inv_in = c->xinv.as<float>();
-    }
+    if (training) a.inv_in = c->xinv.as<float>();
     a.out = out;
     a.P = kQPanel;
     a.queries = true;
@@ -299,7 +298,7 @@ int64_t kvalue_bytes(int64_t nq, int64_t nc) {
 // the weights into the same partial sums.
 SplitPlan plan_split(const ep_ctx* c, int64_t nq, int64_t max_slices, size_t kbytes) {
     const int ms = (int)std::min<int64_t>(kMaxSplits, max_slices);
-    if (c->lt16 <= kMaxFusedTiles) return split_plan(nq, c->n, c->lt16, c->kind, ms);
+    if (c->lt16 <= kMaxFusedTiles) return split_plan(nq, c->n, c->lt16, c->kind, c->any_lolo, ms);
     const int64_t panels = ceil_div(c->n, kCPanel);
     const int64_t fit = (int64_t)(kbytes / kvalue_bytes(nq, kCPanel));
     const int64_t chunks = ceil_div(panels, std::max<int64_t>(1, fit));
@@ -319,6 +318,7 @@ int run_split(ep_ctx* c, const char* Q, const int64_t* qid, int64_t nq, const Sp
     a.nq = nq;
     a.C = c->Xp.as<char>();
     a.c_panel = panel_bytes(kCPanel, c->d);
+    a.lolo = c->any_lolo ? c->lolo.as<int>() : nullptr;
     a.nc = c->n;
     a.nk = feature_steps(c->d);
     a.W = c->wplanes.as<char>();
@@ -346,9 +346,10 @@ int run_split(ep_ctx* c, const char* Q, const int64_t* qid, int64_t nq, const Sp
             const int64_t np = std::min(plan.chunk, panels - p0);
             a.c_base = p0 * kCPanel;
             a.C = c->Xp.as<char>() + p0 * a.c_panel;
+            if (c->any_lolo) a.lolo = c->lolo.as<int>() + p0;
             a.nc = std::min(np * kCPanel, c->n - a.c_base);
             if (capture) a.kpos = c->kpos.as<int>() + a.c_base;
-            HIP_TRY(split_launch(a, split_plan(nq, a.nc, 0, c->kind, 1 << 20), c->stream));
+            HIP_TRY(split_launch(a, split_plan(nq, a.nc, 0, c->kind, c->any_lolo, 1 << 20), c->stream));
             WmulArgs w{};
             w.K = kbuf;
             w.kgroups = a.kgroups;
@@ -719,31 +720,31 @@ int apply_rank(ep_ctx* c, int64_t k) {
     return EP_OK;
 }
 
-// Row norms of the centres, and the split-precision operands (packed
-// centres, zero planes of alpha) where they take at most half of the free
-// device memory: without them every pass runs on float32 operands.
+// The split-precision operands (packed centres, zero planes of alpha), where
+// they take at most half of the free device memory: without them every pass
+// runs on float32 operands.
 int setup_split(ep_ctx* c) {
     const int64_t n = c->n, d = c->d;
     hipStream_t st = c->stream;
     const int64_t lt = ceil_div(c->l, 16);
     c->lt16 = lt;
-    const size_t xp = (size_t)ceil_div(n, kCPanel) * panel_bytes(kCPanel, d);
+    const int64_t panels = ceil_div(n, kCPanel);
+    const size_t xp = (size_t)panels * panel_bytes(kCPanel, d);
     const size_t wp = (size_t)weight_plane_bytes(c->n_pad, c->lt16);
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
     c->split = n < (int64_t(1) << 31) - kCPanel && lt < (1 << 20) && xp + wp <= free_b / 2;
     if (c->split && (c->Xp.ensure(xp) != hipSuccess || c->wplanes.ensure(wp) != hipSuccess ||
-                     c->xinv.ensure((size_t)n * sizeof(float)) != hipSuccess)) {
+                     c->xinv.ensure((size_t)n * sizeof(float)) != hipSuccess ||
+                     c->lolo.ensure((size_t)panels * sizeof(int)) != hipSuccess)) {
         (void)hipGetLastError();       // another allocation took the memory meanwhile
         c->Xp.release();
         c->wplanes.release();
         c->split = false;
     }
-    if (!c->split) {
-        HIP_TRY(launch_row_norms(c->X, n, d, d, c->norms.as<float>(), st));
-        return EP_OK;
-    }
+    if (!c->split) return EP_OK;
     HIP_TRY(launch_fill_f32(c->wplanes.as<float>(), (int64_t)(wp / 4), 0.f, st));
+    HIP_TRY(launch_fill_f32(c->lolo.as<float>(), panels, 0.f, st));
     PackArgs a{};
     a.X = c->X;
     a.n = n;
@@ -751,10 +752,14 @@ int setup_split(ep_ctx* c) {
     a.rows = n;
     a.out = c->Xp.as<char>();
     a.P = kCPanel;
-    a.norms_out = c->norms.as<float>();
     a.inv_out = c->xinv.as<float>();
+    a.lolo = c->lolo.as<int>();
     a.err = c->err.as<int>();
     HIP_TRY(launch_pack_rows(a, st));
+    std::vector<int> lolo((size_t)panels);
+    HIP_TRY(hipMemcpyAsync(lolo.data(), c->lolo.p, lolo.size() * sizeof(int), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    c->any_lolo = std::find(lolo.begin(), lolo.end(), 1) != lolo.end();
     return EP_OK;
 }
 
@@ -817,6 +822,7 @@ int do_setup(ep_ctx* c, const int64_t* sub_idx, uint64_t seed, const double* sig
         HIP_TRY(hipMemcpy(c->kpos.p, kp.data(), (size_t)n * sizeof(int32_t),
                           hipMemcpyHostToDevice));
     }
+    HIP_TRY(launch_row_norms(c->X, n, d, d, c->norms.as<float>(), st));
     if (int rc = setup_split(c)) return rc;
     HIP_TRY(launch_gather_rows(c->X, n, d, c->norms.as<float>(), c->r_dev.as<int64_t>(), s,
                                c->s_pad, c->Xs.as<float>(), c->xs_norms.as<float>(),

@@ -112,20 +112,21 @@ struct KblockArgs {
 hipError_t kblock_launch(const KblockArgs& a, hipStream_t s);
 
 // Split-precision fused pass (skmv.hip; operand layouts in split.h).
-// Packs rows into panels of P rows (two scaled fp16 planes, then P norms and
-// P inverse scales): rows idx[0 .. rows) of X, or rows 0 .. rows - 1.
+// Packs rows into panels of P rows (two scaled fp16 planes, then P norms of
+// the packed values and P inverse scales): rows idx[0 .. rows) of X, or rows
+// 0 .. rows - 1.
 struct PackArgs {
     const float* X;            // row-major, leading dimension d
     int64_t n;                 // rows of X (bound of idx)
     int64_t d;
     const int64_t* idx;        // NULL: identity
     int64_t rows;
-    const float* norms_in;     // per row of X: |x|^2 and inverse scale, or
-    const float* inv_in;       //   both NULL (computed)
+    const float* inv_in;       // inverse scale per row of X (NULL: computed)
     char* out;                 // round_up(rows, P) / P panels
     int64_t P;
-    float* norms_out;          // per packed row (may be NULL)
-    float* inv_out;
+    float* inv_out;            // per packed row (may be NULL)
+    int* lolo;                 // per panel, zero before: 1 where a row's low
+                               //   planes need their own products (may be NULL)
     int* err;                  // set where idx is out of range
     bool queries;              // planes of feature steps [neg0, neg1) negated
     int64_t nk, panel;         // (set by the launch)
@@ -148,6 +149,8 @@ struct SplitArgs {
     int64_t nq;
     const char* C;             // packed centres, panels of kCPanel rows
     int64_t c_panel;
+    const int* lolo;           // per panel of centres: low by low products too
+                               //   (NULL: none)
     int64_t nc;
     int64_t nk;                // 32-feature steps
     int neg0, neg1;            // (sign_steps, set by the launch)
@@ -174,7 +177,8 @@ struct SplitPlan {
     int64_t chunk = 0;         // centre panels per chunk of stored kernel values
 };
 constexpr int kMaxFusedTiles = 10;   // label tiles whose accumulators fit the fused pass
-SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, int max_slices);
+// ll: some panels need the products of the low planes
+SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, bool ll, int max_slices);
 hipError_t split_launch(SplitArgs a, const SplitPlan& p, hipStream_t s);
 
 // out[split][q, j] (+)= sum of K[q, c] W[c, j] over a chunk's centres, from

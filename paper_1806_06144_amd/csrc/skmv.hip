@@ -3,11 +3,12 @@
 //   out[q, :] = sum_j k(q, c_j) W[j, :]      (Algorithm 1 step 2, prediction)
 //
 // the same pass as kmv.hip, with both float32 products replaced by sums of
-// 16-bit products that lose nothing against float32 (split.h): distances as
-// three fp16 products of two planes, the contraction with the weights as six
-// bf16 products of three planes, all accumulated in float32. The fp16 / bf16
-// MFMA runs 16 times as many products per cycle as the fp32 one, so the
-// distance product costs 3/16 and the contraction 6/16 of what it did.
+// 16-bit products (split.h says what these keep): distances as three fp16
+// products of two planes, four where rows need it, the contraction with the
+// weights as six bf16 products of three planes, all accumulated in float32.
+// The fp16 / bf16 MFMA runs 16 times as many products per cycle as the fp32
+// one, so the distance product costs 3/16 and the contraction 6/16 of what it
+// did.
 //
 // Bound by the 16-bit MFMA rate under this card's power limit (a large
 // library product reaches 1.14 to 1.36 of the nominal 2.5 PFLOP/s). Of it
@@ -43,13 +44,15 @@ constexpr int kSlotQuads = kCPanel / 16 * 2 * 64;    // 16-byte quads of one 32-
 
 // ---- packing ---------------------------------------------------------------
 
-// Packs 16 rows per workgroup: norms (float64 sums, as row_norms_kernel) and
-// row maxima first unless they are given, then the two scaled fp16 planes.
-// Rows past `rows` and gathered rows out of [0, n) are zero (norm 0, scale 1).
+// Packs 16 rows per workgroup: row maxima first unless the scales are given,
+// then the two scaled fp16 planes, and from them the norms of the packed rows
+// (float64 sums of (hi + lo)^2). Rows past `rows` and gathered rows out of
+// [0, n) are zero (norm 0, scale 1).
 template <bool VEC>
 __global__ void __launch_bounds__(1024) pack_rows_kernel(PackArgs p) {
-    __shared__ float s_norm[16], s_inv[16], s_scale[16];
+    __shared__ float s_inv[16];
     __shared__ int64_t s_row[16];
+    __shared__ double s_sum[16][2][16];              // [wave][(hi + lo)^2, lo^2][row]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
     const int64_t tiles = (p.rows + p.P - 1) / p.P * (p.P / 16);
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
@@ -64,61 +67,42 @@ __global__ void __launch_bounds__(1024) pack_rows_kernel(PackArgs p) {
                 }
             }
             s_row[tid] = src;
-            if (p.norms_in) {
-                s_norm[tid] = src >= 0 ? p.norms_in[src] : 0.f;
-                s_inv[tid] = src >= 0 ? p.inv_in[src] : 1.f;
-            }
+            if (p.inv_in) s_inv[tid] = src >= 0 ? p.inv_in[src] : 1.f;
         }
         __syncthreads();
-        if (!p.norms_in) {
+        if (!p.inv_in) {
             for (int r = wave; r < 16; r += waves) {
                 const int64_t src = s_row[r];
-                double acc = 0.0;
                 float mx = 0.f;
                 if (src >= 0) {
                     const float* x = p.X + src * p.d;
-                    for (int64_t j = lane; j < p.d; j += 64) {
-                        const float f = x[j];
-                        const double v = f;
-                        acc += v * v;
-                        mx = fmaxf(mx, fabsf(f));
+                    for (int64_t j = lane; j < p.d; j += 512) {
+                        float v[8];                  // (eight loads in flight; repeats of the last)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) v[e] = x[min(j + 64 * e, p.d - 1)];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(v[e]));
                     }
                 }
-                for (int off = 32; off > 0; off >>= 1) {
-                    acc += __shfl_down(acc, off, 64);
-                    mx = fmaxf(mx, __shfl_down(mx, off, 64));
-                }
+                for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_down(mx, off, 64));
                 if (lane == 0) {
                     // largest element into [2^14, 2^15); exponents below -63
                     // (squares below the float32 range) share one scale
-                    const int e = mx == 0.f ? 14
-                                            : min(127, max(-63, (int)(__builtin_bit_cast(unsigned, mx) >> 23) - 127));
-                    s_norm[r] = (float)acc;
+                    const int e =
+                        mx == 0.f ? 14
+                                  : min(127, max(-63, (int)(__builtin_bit_cast(unsigned, mx) >> 23) - 127));
                     s_inv[r] = __builtin_bit_cast(float, (unsigned)(e - 14 + 127) << 23);
                 }
             }
             __syncthreads();
         }
-        if (tid < 16) {
-            // a power of two: its reciprocal is exact
-            s_scale[tid] = 1.f / s_inv[tid];
-            const int64_t b = tile * 16 + tid;
-            const int64_t panel = b / p.P, at = b % p.P;
-            float* meta = reinterpret_cast<float*>(p.out + panel * p.panel + p.nk * (p.P / 16) * 2 * kFragBytes);
-            meta[at] = s_norm[tid];
-            meta[p.P + at] = s_inv[tid];
-            if (b < p.rows) {
-                if (p.norms_out) p.norms_out[b] = s_norm[tid];
-                if (p.inv_out) p.inv_out[b] = s_inv[tid];
-            }
-        }
-        __syncthreads();
         const int row = lane & 15, g = lane >> 4;
         const int64_t src = s_row[row];
-        const float sc = s_scale[row];
+        const float sc = 1.f / s_inv[row];     // (a power of two: exact)
         const float* x = p.X + (src >= 0 ? src : 0) * p.d;
         const int64_t t_panel = p.P / 16;
         char* out = p.out + (tile / t_panel) * p.panel + (tile % t_panel) * 2 * kFragBytes + lane * 16;
+        double sum = 0.0, sum_lo = 0.0;
         for (int64_t ks = wave; ks < p.nk; ks += waves) {
             const int64_t c0 = ks * 32 + 8 * g;
             const float sck = ks >= p.neg0 && ks < p.neg1 ? -sc : sc;
@@ -126,7 +110,8 @@ __global__ void __launch_bounds__(1024) pack_rows_kernel(PackArgs p) {
             if (VEC) {
                 const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
                 const float4 a = src >= 0 && c0 < p.d ? *reinterpret_cast<const float4*>(x + c0) : z;
-                const float4 b = src >= 0 && c0 + 4 < p.d ? *reinterpret_cast<const float4*>(x + c0 + 4) : z;
+                const float4 b =
+                    src >= 0 && c0 + 4 < p.d ? *reinterpret_cast<const float4*>(x + c0 + 4) : z;
                 v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
                 v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
             } else {
@@ -140,12 +125,51 @@ __global__ void __launch_bounds__(1024) pack_rows_kernel(PackArgs p) {
                 const _Float16 h = (_Float16)s;
                 hi[j] = h;
                 lo[j] = __builtin_isfinite(s) ? (_Float16)(s - (float)h) : (_Float16)0.f;
+                const double ql = (double)(float)lo[j], q = (double)(float)h + ql;
+                sum += q * q;
+                if (p.lolo) sum_lo += ql * ql;
             }
             char* o = out + ks * t_panel * 2 * kFragBytes;
             *reinterpret_cast<half8*>(o) = hi;
             *reinterpret_cast<half8*>(o + kFragBytes) = lo;
         }
-        __syncthreads();               // the next tile overwrites the rows and scales
+        for (int off = 32; off >= 16; off >>= 1) {
+            sum += __shfl_down(sum, off, 64);
+            sum_lo += __shfl_down(sum_lo, off, 64);
+        }
+        if (lane < 16) {
+            s_sum[wave][0][lane] = sum;
+            s_sum[wave][1][lane] = sum_lo;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            double sq = 0.0, sl = 0.0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int w = 4 * e + g;
+                if (w < waves) {
+                    sq += s_sum[w][0][row];
+                    sl += s_sum[w][1][row];
+                }
+            }
+            for (int off = 32; off >= 16; off >>= 1) {
+                sq += __shfl_down(sq, off, 64);
+                sl += __shfl_down(sl, off, 64);
+            }
+            if (lane < 16) {
+                const float inv = s_inv[lane];
+                const int64_t b = tile * 16 + lane;
+                const int64_t panel = b / p.P, at = b % p.P;
+                float* meta = reinterpret_cast<float*>(p.out + panel * p.panel +
+                                                       p.nk * (p.P / 16) * 2 * kFragBytes);
+                meta[at] = (float)(sq * inv * inv);
+                meta[p.P + at] = inv;
+                if (p.inv_out && b < p.rows) p.inv_out[b] = inv;
+                // (the same value from every row that needs it)
+                if (p.lolo && sl > kLoLoMax * sq) p.lolo[panel] = 1;
+            }
+        }
+        __syncthreads();               // the next tile overwrites rows, scales, sums
     }
 }
 
@@ -177,7 +201,11 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float* W, int64
 // LT = 0: the kernel values themselves are the result, written as the operand
 // planes of wmul_kernel (16 queries x 32 centres, three bf16 planes; those of
 // odd 32-centre groups negated).
-template <int KIND, int LT, int QB, int CW>
+// LL: some panels of centres need the products of the low planes (split.h).
+// The branch alone costs 5 to 8 % where the accumulators fill the registers
+// (10 labels, 60000 x 784: 1310 queries 456 -> 479 us, 10000 queries 2044 ->
+// 2207 us), so problems without such a panel run without it.
+template <int KIND, int LT, int QB, int CW, bool LL>
 __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
     static_assert(CW == 8 || LT > 0, "stored kernel values: CW = 8");
     constexpr int kWQ = 16 * QB;                     // queries per wave
@@ -265,6 +293,7 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
 #pragma unroll
         for (int b = 0; b < QB; ++b) oacc[c][b] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+    [[maybe_unused]] int lolo = 0;                   // low by low products of this panel
     auto step = [&](auto tag, __amdgpu_buffer_rsrc_t crs, int ks) {
         constexpr int S = decltype(tag)::value;
         // the queries' planes change sign here (sign_steps)
@@ -288,6 +317,10 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
                 a[(c + 1) & 1][1] = xs[(2 * c + 3) * 64 + lane];
             }
             const uintx4 ah = a[c & 1][0], al = a[c & 1][1];
+            if (LL && lolo) {
+#pragma unroll
+                for (int i = 0; i < QB; ++i) sacc[c][i] = mfma_f16(al, b[i][1], sacc[c][i]);
+            }
 #pragma unroll
             for (int i = 0; i < QB; ++i) sacc[c][i] = mfma_f16(al, b[i][0], sacc[c][i]);
 #pragma unroll
@@ -319,6 +352,7 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
     float4 meta = make_float4(0.f, 0.f, 0.f, 0.f);
     int kp[2] = {-1, -1};
     auto load_meta = [&](int t) {
+        if (LL) lolo = __builtin_amdgcn_readfirstlane(p.lolo[t]);
         if (wave == 0)
             meta = *reinterpret_cast<const float4*>(p.C + t * p.c_panel +
                                                     (int64_t)nk * 16 * kFragBytes + lane * 16);
@@ -653,27 +687,32 @@ __global__ void __launch_bounds__(kSThreads, 2) wmul_kernel(WmulArgs p) {
 
 typedef void (*SplitFn)(SplitArgs);
 
-template <int KIND, int CW>
+template <int KIND, int CW, bool LL>
 SplitFn fused_fn(int lt) {
     switch (lt) {
-        case 1: return skmv_kernel<KIND, 1, 4, CW>;
-        case 2: return skmv_kernel<KIND, 2, 2, CW>;
-        case 3: return skmv_kernel<KIND, 3, 2, CW>;
-        case 4: return skmv_kernel<KIND, 4, 2, CW>;
-        case 5: return skmv_kernel<KIND, 5, 2, CW>;
-        case 6: return skmv_kernel<KIND, 6, 2, CW>;
-        case 7: return skmv_kernel<KIND, 7, 2, CW>;
-        case 8: return skmv_kernel<KIND, 8, 2, CW>;
-        case 9: return skmv_kernel<KIND, 9, 2, CW>;
-        default: return skmv_kernel<KIND, 10, 2, CW>;
+        case 1: return skmv_kernel<KIND, 1, 4, CW, LL>;
+        case 2: return skmv_kernel<KIND, 2, 2, CW, LL>;
+        case 3: return skmv_kernel<KIND, 3, 2, CW, LL>;
+        case 4: return skmv_kernel<KIND, 4, 2, CW, LL>;
+        case 5: return skmv_kernel<KIND, 5, 2, CW, LL>;
+        case 6: return skmv_kernel<KIND, 6, 2, CW, LL>;
+        case 7: return skmv_kernel<KIND, 7, 2, CW, LL>;
+        case 8: return skmv_kernel<KIND, 8, 2, CW, LL>;
+        case 9: return skmv_kernel<KIND, 9, 2, CW, LL>;
+        default: return skmv_kernel<KIND, 10, 2, CW, LL>;
     }
 }
+template <int KIND, bool LL>
+SplitFn kind_fn(int lt, int cw) {
+    if (lt == 0) return skmv_kernel<KIND, 0, 4, 8, LL>;
+    if (cw == 2) return fused_fn<KIND, 2, LL>(lt);
+    if (cw == 4) return fused_fn<KIND, 4, LL>(lt);
+    return fused_fn<KIND, 8, LL>(lt);
+}
 // Kernel for lt label tiles (0: kernel values) and cw blocks per wave.
-SplitFn split_fn(int kind, int lt, int cw) {
-    if (lt == 0) return kind == 0 ? skmv_kernel<0, 0, 4, 8> : skmv_kernel<1, 0, 4, 8>;
-    if (cw == 2) return kind == 0 ? fused_fn<0, 2>(lt) : fused_fn<1, 2>(lt);
-    if (cw == 4) return kind == 0 ? fused_fn<0, 4>(lt) : fused_fn<1, 4>(lt);
-    return kind == 0 ? fused_fn<0, 8>(lt) : fused_fn<1, 8>(lt);
+SplitFn split_fn(int kind, int lt, int cw, bool ll) {
+    if (ll) return kind == 0 ? kind_fn<0, true>(lt, cw) : kind_fn<1, true>(lt, cw);
+    return kind == 0 ? kind_fn<0, false>(lt, cw) : kind_fn<1, false>(lt, cw);
 }
 
 // Queries per workgroup: with one label tile the accumulators leave room for
@@ -734,12 +773,12 @@ hipError_t launch_pack_weights(const float* W, int64_t rows, int64_t l, int64_t 
     return hipGetLastError();
 }
 
-SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, int max_slices) {
+SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, bool ll, int max_slices) {
     // the fewest centre blocks per wave whose tile still holds all queries
     int cw = 8;
     if (lt > 0)
         while (cw > 2 && split_rows(lt, cw / 2) >= nq) cw /= 2;
-    const int64_t slots = split_slots(split_fn(kind, (int)lt, cw));
+    const int64_t slots = split_slots(split_fn(kind, (int)lt, cw, ll));
     const int64_t tq = ceil_div(std::max<int64_t>(nq, 1), split_rows(lt, cw));
     const int64_t nt = ceil_div(std::max<int64_t>(nc, 1), kCPanel);
     SplitPlan best{1, nt, 0.0};
@@ -797,7 +836,8 @@ hipError_t split_launch(SplitArgs a, const SplitPlan& p, hipStream_t s) {
     a.tps = p.tps;
     sign_steps(a.nk, &a.neg0, &a.neg1);
     const int64_t tq = ceil_div(std::max<int64_t>(a.nq, 1), split_rows(a.lt, p.cw));
-    hipLaunchKernelGGL(split_fn(a.kind, a.lt, p.cw), dim3((unsigned)(tq * p.splits)), dim3(kSThreads), 0, s, a);
+    hipLaunchKernelGGL(split_fn(a.kind, a.lt, p.cw, a.lolo != nullptr), dim3((unsigned)(tq * p.splits)),
+                       dim3(kSThreads), 0, s, a);
     return hipGetLastError();
 }
 

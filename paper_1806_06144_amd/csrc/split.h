@@ -3,11 +3,30 @@
 //
 // Feature rows. A float32 row x is scaled by a power of two so that its
 // largest element lies in [2^14, 2^15) and stored as two fp16 planes, hi =
-// fp16(x), lo = fp16(x - hi). hi + lo keeps 22 to 24 significant bits of
-// every element down to 2^-40 of the row's largest, so a dot product formed
-// as hi.hi + hi.lo + lo.hi (exact products, float32 accumulation) is off by
-// less than the rounding of a float32 accumulation. The scale is undone
-// exactly (a power of two) when the distance is formed.
+// fp16(x), lo = fp16(x - hi). hi + lo is x to 2^-23 of an element, and to
+// 2^-39 of the row's largest element for those below 2^-16 of it. What is
+// computed is the distance between packed rows: their norms are summed (in
+// float64) from hi + lo, so rows that share values, however large, are not
+// moved apart by their rounding.
+//
+// The dot product is formed as lo.hi + hi.lo + hi.hi (exact products, float32
+// accumulation). The fourth term moves a squared distance by 2 lo_x.lo_z, at
+// most |lo_x|^2 + |lo_z|^2. For most rows |lo|^2 is 0.6 to 0.7 of 2^-24 |x|^2,
+// about the rounding of the norms themselves, but a row dominated by a few
+// values that lie badly between fp16 numbers has up to 2^-22, and rows that
+// share them are all moved alike. Panels of centres with a row above kLoLoMax
+// are therefore multiplied with the fourth product too.
+//
+// Errors against float64 with float32 operands, with three products and norms
+// of the unpacked rows, and as above: squared distances of 16 normal features
+// beside a constant column of 64.03, root mean square in units of 2^-24 of the
+// norms, 2.3 (0.9 with the column last), 8.6, 2.0; 64 features with it 4.2,
+// 8.8, 2.7; 784 with it 11.4, 10.1, 7.0; 784 normal features 1.34, 1.31, 1.31;
+// 784 uniform 5.3, 3.3, 3.3 (an instruction takes 32 features, so the
+// accumulator is rounded d / 32 times, not d / 2). Rows of few features show
+// the packing: 12 of 784 features 0.61, 0.61, 0.83. Sums over 20000 to 43000
+// centres, relative: 16 features and the column 7.3e-5, 2.6e-4, 6.7e-5;
+// without it 4.1e-7, 1.8e-7, 1.9e-7; 12 of 784 features 4.8e-7, 2.1e-7, 2.1e-7.
 //
 // Weights and kernel values (no common scale: both may span the whole
 // float32 range) are stored as three bf16 planes, hi + mid + lo, which
@@ -29,6 +48,10 @@ namespace ep {
 constexpr int kFragBytes = 1024;      // one 16 x 32 operand plane
 constexpr int kCPanel = 128;          // centre rows per packed panel
 constexpr int kQPanel = 64;           // query rows per packed panel
+
+// Bound of |lo|^2 / |x|^2 up to which lo.lo is left out: with both rows below
+// it, it is at most 2^-24 of the norms.
+constexpr double kLoLoMax = 1.0 / (1 << 24);
 
 // 32-deep feature steps of a row of d features.
 inline __host__ __device__ int64_t feature_steps(int64_t d) { return (d + 31) / 32; }

@@ -175,3 +175,78 @@ def test_correction_chunks(s, m, k, l):
         g.set_alpha(a0)
         g.step(t, Y[t])
         assert rel(g.alpha() - a0, a_o - a0) < TOL_STEP
+
+
+def _rows(law, d, n, rng):
+    if law == "two":             # 0 or a value midway between two fp16 numbers
+        return (rng.random((n, d)) < 0.5) * np.float32(1.0 + 2.0 ** -11 + 2.0 ** -13)
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    if law.startswith("column"):
+        value, at = law.split()[1:]
+        x[:, int(float(at) * (d - 1))] = np.float32(value)
+    if law == "sparse":          # few features, so no sum evens the rounding out
+        x *= rng.random((n, d)) < 12.0 / d
+    return x.astype(np.float32)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [16, 64, 784])
+@pytest.mark.parametrize("law", ["normal", "two", "sparse", "column 64.0312 0", "column 64.0312 1",
+                                 "column 33.015 0.5", "column 65.03 0", "near"])
+def test_distances_are_as_good_as_float32(law, d):
+    """Squared distances, read off the kernel values of single centres, of
+    rows that share large values or lie close together: their error against
+    float64 is no larger than that of a float32 chain over the features, in
+    the worse of two orders (a large value met first costs every later addition
+    a rounding at its size), neither its root mean square nor its mean, which
+    would move all kernel values alike. Allowed beside it: what packing a row
+    to 2^-23 adds (computed from the packed values) and, as an accumulator of
+    the 16-bit matrix cores is truncated where the chain is rounded, a tenth."""
+    n, nz, l = int(2 ** 27 / (256 * d) * 1.3) + 77, 256, 32
+    rng = np.random.default_rng(d)
+    X = _rows("normal" if law == "near" else law, d, n, rng)
+    Z = _rows("normal" if law == "near" else law, d, nz, rng)
+    pair = np.ones((nz, l), dtype=bool)
+    if law == "near":
+        Z = (X[np.arange(nz) % l] + 2.0 ** -9 * rng.standard_normal((nz, d))).astype(np.float32)
+        pair = np.arange(nz)[:, None] % l == np.arange(l)[None]
+    x, z = X[:l], Z
+    d2 = np.stack([((z.astype(np.float64) - r) ** 2).sum(1) for r in x.astype(np.float64)], 1)
+    xn, zn = (x.astype(np.float64) ** 2).sum(1), (z.astype(np.float64) ** 2).sum(1)
+    unit = EPS * (zn[:, None] + xn[None])
+    pair &= unit > 0
+
+    def chain(order):            # norms rounded from float64, one rounding a product
+        dot = np.zeros((nz, l), dtype=np.float32)
+        for j in order:
+            dot = (dot + z[:, j, None].astype(np.float64) * x[None, :, j]).astype(np.float32)
+        return (zn.astype(np.float32)[:, None] + xn.astype(np.float32)[None]) - np.float32(2) * dot
+
+    # distance of the packed rows (no element here is below 2^-16 of its row's
+    # largest by more than the fp16 range, so the row's scale does not matter)
+    def packed(r):
+        h = r.astype(np.float16).astype(np.float32)
+        return h.astype(np.float64) + (r - h).astype(np.float16)
+
+    p2 = np.stack([((packed(z) - r) ** 2).sum(1) for r in packed(x)], 1)
+    bw = bw32(np.sqrt(d2[pair].mean() / 8))
+    a = np.zeros((n, l), dtype=np.float32)
+    a[np.arange(l), np.arange(l)] = 1.0
+    assert -(-nz // 64) * 64 * n * d > 2 ** 27
+    with Gpu(X, l, "gaussian", bw, 20, 2, np.arange(100, 120)) as g:
+        g.set_alpha(a)
+        K = g.predict(Z).astype(np.float64)
+    scale = np.float64(np.float32(np.log2(np.e) / (2 * bw * bw)))
+    ok = pair & (K > 0)
+    assert ok.sum() > 0.9 * pair.sum()
+    err = ((-np.log2(K[ok]) / scale) - d2[ok]) / unit[ok]
+    ref = [(chain(order)[ok] - d2[ok]) / unit[ok] for order in (range(d), range(d - 1, -1, -1))]
+    # what reading a distance off its kernel value adds: the rounding of exp2's
+    # argument (uniform, 0.3 of its unit) and of exp2 (0.6)
+    read = np.sqrt((((0.6 * 2 * bw * bw) ** 2 + (0.4 * d2[ok]) ** 2) * (EPS / unit[ok]) ** 2).mean())
+    rms, rms_f32 = np.sqrt((err ** 2).mean()), max(np.sqrt((r ** 2).mean()) for r in ref)
+    bias, bias_f32 = abs(err.mean()), max(abs(r.mean()) for r in ref)
+    print(law, d, "rms", rms, "float32", rms_f32, "read", read, "mean", bias, bias_f32)
+    pack = np.sqrt((((p2 - d2)[ok] / unit[ok]) ** 2).mean())
+    assert rms <= 1.1 * np.sqrt(rms_f32 ** 2 + read ** 2 + pack ** 2)
+    assert bias <= bias_f32 + 1.0
