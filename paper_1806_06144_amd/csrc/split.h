@@ -111,15 +111,21 @@ inline __host__ __device__ int64_t weight_plane_bytes(int64_t n_pad, int64_t lt)
     return (n_pad / 32) * lt * 3 * kFragBytes;
 }
 // Stores the three planes of one weight. Values that round up to infinity
-// in bf16 keep their largest finite head.
+// in bf16 keep their largest finite head. Infinities and NaN go into the low
+// plane, which meets only the heads of kernel values: a head times infinity is
+// infinite, as in float32, where a zero mid or low plane would make it NaN.
 __device__ __forceinline__ void store_weight(unsigned short* planes, int64_t at, float w) {
-    unsigned h = pack_bf16(w, 0.f) & 0xffffu;
-    if ((h & 0x7fffu) == 0x7f80u && __builtin_isfinite(w)) h -= 1;
-    float r = w - bf16_lo(h);
-    if ((h & 0x7f80u) == 0x7f80u) r = 0.f;      // infinity, NaN: in the head alone
-    const unsigned m = pack_bf16(r, 0.f) & 0xffffu;
-    r -= bf16_lo(m);
-    const unsigned l = pack_bf16(r, 0.f) & 0xffffu;
+    unsigned h = 0, m = 0, l = 0;
+    if (__builtin_isfinite(w)) {
+        h = pack_bf16(w, 0.f) & 0xffffu;
+        if ((h & 0x7fffu) == 0x7f80u) h -= 1;
+        float r = w - bf16_lo(h);
+        m = pack_bf16(r, 0.f) & 0xffffu;
+        r -= bf16_lo(m);
+        l = pack_bf16(r, 0.f) & 0xffffu;
+    } else {
+        l = pack_bf16(w, 0.f) & 0xffffu;
+    }
     planes[at] = (unsigned short)h;
     planes[at + 512] = (unsigned short)m;
     planes[at + 1024] = (unsigned short)l;

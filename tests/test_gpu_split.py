@@ -250,3 +250,29 @@ def test_distances_are_as_good_as_float32(law, d):
     pack = np.sqrt((((p2 - d2)[ok] / unit[ok]) ** 2).mean())
     assert rms <= 1.1 * np.sqrt(rms_f32 ** 2 + read ** 2 + pack ** 2)
     assert bias <= bias_f32 + 1.0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("l", [5, 300])
+@pytest.mark.parametrize("n_z", [1, 64, 300])
+def test_infinite_weights(l, n_z):
+    """Infinite and NaN weights reach the results of their own labels only,
+    an infinity as an infinity, by either form of the contraction."""
+    n, d, bw = 128 * 300 + 5, 64, bw32(9.0)
+    rng = np.random.default_rng(l + n_z)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    Z = rng.standard_normal((n_z, d)).astype(np.float32)
+    a = rng.standard_normal((n, l)).astype(np.float32)
+    a[31, 0], a[128 * 200 + 40, 1], a[n - 1, 2] = np.inf, -np.inf, np.nan
+    a[5, l - 1], a[n // 2, l - 1] = np.inf, np.inf
+    assert -(-n_z // 64) * 64 * n * d > 2 ** 27
+    with Gpu(X, l, "gaussian", bw, 20, 2, np.arange(20)) as g:
+        g.set_alpha(a)
+        P = g.predict(Z)
+    assert np.all(P[:, 0] == np.inf) and np.all(P[:, 1] == -np.inf)
+    assert np.all(np.isnan(P[:, 2])) and np.all(P[:, l - 1] == np.inf)
+    some = slice(3, 4)
+    P_o = oracle.predict(X.astype(np.float64), a[:, some].astype(np.float64), Z.astype(np.float64),
+                         oracle.GAUSSIAN, bw)
+    assert np.max(np.abs(P[:, some] - P_o) / _bound(X, Z, a[:, some], "gaussian", bw)) <= 1.0
+    assert np.all(np.isfinite(P[:, 3:l - 1]))
