@@ -86,26 +86,29 @@ __global__ void __launch_bounds__(1024) pack_rows_kernel(PackArgs p) {
                 }
                 for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_down(mx, off, 64));
                 if (lane == 0) {
-                    // largest element into [2^14, 2^15); exponents below -63
-                    // (squares below the float32 range) share one scale
+                    // largest element into [2^14, 2^15); exponents below -49
+                    // share one scale, so that the product of two inverse
+                    // scales stays a normal float32 (2^-63, whose square is
+                    // the smallest normal one, still has 24 bits in lo)
                     const int e =
-                        mx == 0.f ? 14
-                                  : min(127, max(-63, (int)(__builtin_bit_cast(unsigned, mx) >> 23) - 127));
-                    s_inv[r] = __builtin_bit_cast(float, (unsigned)(e - 14 + 127) << 23);
+                        mx == 0.f ? 14 : max(-49, (int)(__builtin_bit_cast(unsigned, mx) >> 23) - 127);
+                    s_inv[r] = mx == __builtin_inff()
+                                   ? mx
+                                   : __builtin_bit_cast(float, (unsigned)(e - 14 + 127) << 23);
                 }
             }
             __syncthreads();
         }
         const int row = lane & 15, g = lane >> 4;
         const int64_t src = s_row[row];
-        const float sc = 1.f / s_inv[row];     // (a power of two: exact)
+        const float sc = 1.f / s_inv[row];     // (a power of two: exact; zero for an infinite row)
         const float* x = p.X + (src >= 0 ? src : 0) * p.d;
         const int64_t t_panel = p.P / 16;
         char* out = p.out + (tile / t_panel) * p.panel + (tile % t_panel) * 2 * kFragBytes + lane * 16;
         double sum = 0.0, sum_lo = 0.0;
         for (int64_t ks = wave; ks < p.nk; ks += waves) {
             const int64_t c0 = ks * 32 + 8 * g;
-            const float sck = ks >= p.neg0 && ks < p.neg1 ? -sc : sc;
+            const float flip = ks >= p.neg0 && ks < p.neg1 ? -1.f : 1.f;
             float v[8];
             if (VEC) {
                 const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -121,10 +124,14 @@ __global__ void __launch_bounds__(1024) pack_rows_kernel(PackArgs p) {
             half8 hi, lo;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const float s = v[j] * sck;
+                float s = v[j] * sc * flip;
+                if (!__builtin_isfinite(v[j])) {
+                    s = __builtin_isinf(v[j]) ? __builtin_copysignf(flip, v[j] * flip) : 0.f;
+                    if (v[j] != v[j]) sum += v[j];
+                }
                 const _Float16 h = (_Float16)s;
                 hi[j] = h;
-                lo[j] = __builtin_isfinite(s) ? (_Float16)(s - (float)h) : (_Float16)0.f;
+                lo[j] = (_Float16)(s - (float)h);
                 const double ql = (double)(float)lo[j], q = (double)(float)h + ql;
                 sum += q * q;
                 if (p.lolo) sum_lo += ql * ql;
@@ -339,7 +346,8 @@ __global__ void __launch_bounds__(kSThreads, 2) skmv_kernel(SplitArgs p) {
     };
 
     auto value = [&](float s, float cn, float ci, int b) {
-        return kernel_value<KIND>(fmaf(s * ci, iq2[b], qn[b] + cn), p.scale);
+        // (the scales first: their product overflows only where the distance does)
+        return kernel_value<KIND>(fmaf(s, ci * iq2[b], qn[b] + cn), p.scale);
     };
 
     auto prefetch = [&](int t) {

@@ -28,6 +28,11 @@
 // centres, relative: 16 features and the column 7.3e-5, 2.6e-4, 6.7e-5;
 // without it 4.1e-7, 1.8e-7, 1.9e-7; 12 of 784 features 4.8e-7, 2.1e-7, 2.1e-7.
 //
+// A row that holds an infinity is stored as its infinite elements alone, +-1,
+// with an infinite norm and inverse scale: its distances come out infinite
+// where the dot product is negative and NaN (taken as 0) elsewhere, as those
+// of float32 operands do. NaN elements make the norm NaN.
+//
 // Weights and kernel values (no common scale: both may span the whole
 // float32 range) are stored as three bf16 planes, hi + mid + lo, which
 // represent a float32 exactly; of the nine products the six largest are

@@ -276,3 +276,49 @@ def test_infinite_weights(l, n_z):
                          oracle.GAUSSIAN, bw)
     assert np.max(np.abs(P[:, some] - P_o) / _bound(X, Z, a[:, some], "gaussian", bw)) <= 1.0
     assert np.all(np.isfinite(P[:, 3:l - 1]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kernel", ["gaussian", "laplacian"])
+def test_features_beyond_the_float32_squares(kernel):
+    """Rows with an infinite or NaN feature, or whose squares overflow, give
+    what the float32 expansion |x|^2 + |z|^2 - 2 x.z gives, with a NaN distance
+    taken as 0: for queries and for centres."""
+    n, d, n_z, bw = 128 * 300 + 5, 64, 130, bw32(9.0)
+    rng = np.random.default_rng(3)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    Z = rng.standard_normal((n_z, d)).astype(np.float32)
+    special = [np.inf, -np.inf, np.nan, np.float32(1e36), np.float32(-1e22)]
+    for i, v in enumerate(special):
+        Z[10 * i, 7] = v
+        X[128 * 50 + 10 * i, 9] = v
+    Z[60] = 1e25
+    X[3000] = -1e25
+    with np.errstate(all="ignore"):
+        f = np.float32
+        d2 = ((Z * Z).sum(1, dtype=f)[:, None] + (X * X).sum(1, dtype=f)[None]
+              - f(2) * np.matmul(Z, X.T))
+    odd_z = [10 * i for i in range(5)] + [60]
+    odd_x = [128 * 50 + 10 * i for i in range(5)] + [3000]
+    rows = np.setdiff1d(np.arange(n_z), odd_z)
+    a = np.zeros((n, 8), dtype=np.float32)
+    for j, c in enumerate(odd_x):            # the kernel values of the odd centres
+        a[c, j] = 1.0
+    a[rng.integers(0, n, 200), 6] = rng.standard_normal(200).astype(np.float32)
+    a[odd_x, 6] = 0.0
+    a[12345, 7] = 1.0
+    with Gpu(X, 8, kernel, bw, 20, 2, np.arange(20)) as g:
+        g.set_alpha(a)
+        P = g.predict(Z)
+    D = np.where(np.isnan(d2), 0.0, np.maximum(d2, 0.0)).astype(np.float64)
+    K = np.exp(-D / (2 * bw * bw)) if kernel == "gaussian" else np.exp(-np.sqrt(D) / bw)
+    want = K @ a.astype(np.float64)
+    assert np.all(np.isfinite(P))
+    # every value of an odd row or centre is 0 or 1 exactly
+    assert np.array_equal(P[rows][:, :6], want[rows][:, :6])
+    assert set(np.unique(want[rows][:, :6])) == {0.0, 1.0}
+    assert np.array_equal(P[odd_z][:, 7], want[odd_z][:, 7])
+    assert np.max(np.abs(P[odd_z][:, 6] - want[odd_z][:, 6])) < 1e-4
+    ref = oracle.predict(X[a[:, 6] != 0].astype(np.float64), a[a[:, 6] != 0][:, 6:7].astype(np.float64),
+                         Z[rows].astype(np.float64), kernel_id(kernel), bw)
+    assert rel(P[rows][:, 6:7], ref) < TOL_STEP
