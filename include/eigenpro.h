@@ -105,8 +105,8 @@ typedef struct ep_setup_opts {
  *
  *   ctx        out: new context (NULL on failure).
  *   X          device, n x d, row-major float32 training features (the
- *              kernel centres). BORROWED: never copied, must stay alive and
- *              unchanged until ep_destroy.
+ *              kernel centres). BORROWED: must stay alive and unchanged until
+ *              ep_destroy.
  *   n, d, l    centres, feature dimension, label columns; each >= 1,
  *              d <= 2^20.
  *   kernel     EP_GAUSSIAN or EP_LAPLACIAN; bandwidth > 0 and finite.
@@ -117,6 +117,14 @@ typedef struct ep_setup_opts {
  *              indices uniformly without replacement from `seed`.
  *   hip_stream hipStream_t to enqueue all work on (NULL = default stream).
  *   info       out (may be NULL): see ep_info.
+ * Memory: a context holds alpha (n x l floats, l rounded up to 32) and, for
+ * the passes on the 16-bit matrix cores, a packed copy of X (4 n d bytes, d
+ * rounded up to 32) and the planes of alpha (6 n l bytes, l rounded up to 16).
+ * These last two are optional: setup makes them, after its own work, where
+ * they take at most half of the free device memory, and a later call whose
+ * buffers do not fit beside them gives them up for good. Without them the
+ * passes run on float32 operands: the same results up to float32 rounding,
+ * two to five times slower. Buffers of the calls are kept and grow on demand.
  * Sets alpha = 0. Blocks until setup is complete. K_s is formed in float64;
  * the eigensolve runs on the device in float64 with EP_SOLVER_AUTO (see
  * ep_setup_ex).

@@ -164,6 +164,26 @@ int max_slices_for(int64_t rows_pad, int64_t ldw, int most = 256) {
 // 595 us for 48 rows and 1.1 M centres of 440 features).
 constexpr int kMaxSplits = 512;
 
+// Gives up the split operands and the buffers of their pass: from here on the
+// context's passes run on float32 operands.
+void drop_split(ep_ctx* c) {
+    (void)hipGetLastError();
+    (void)hipStreamSynchronize(c->stream);
+    for (DevBuf* b : {&c->Xp, &c->xinv, &c->lolo, &c->wplanes, &c->Qp, &c->kbuf}) b->release();
+    c->split = false;
+}
+
+// Room in a buffer that the call cannot do without, for which the split
+// operands are given up where device memory is short.
+hipError_t need(ep_ctx* c, DevBuf& b, size_t bytes) {
+    hipError_t e = b.ensure(bytes);
+    if (e == hipErrorOutOfMemory && c->split) {
+        drop_split(c);
+        e = b.ensure(bytes);
+    }
+    return e;
+}
+
 int record(hipStream_t s, std::vector<TimedPair>& v, bool start) {
     if (start) {
         TimedPair p;
@@ -187,7 +207,7 @@ int run_kmv(ep_ctx* c, const float* Q, int64_t ldq, const float* qn, const int64
     KmvPlan plan =
         kmv_plan(nq, nc, ldc, c->l_pad, c->l, c->kind, max_slices_for(*rows_pad, c->l_pad));
     *slices = plan.slices();
-    HIP_TRY(c->part.ensure((size_t)plan.slices() * (size_t)(*rows_pad) * c->l_pad * sizeof(float)));
+    HIP_TRY(need(c, c->part, (size_t)plan.slices() * (size_t)(*rows_pad) * c->l_pad * sizeof(float)));
     KmvArgs a{};
     a.Q = Q;
     a.ldq = ldq;
@@ -370,27 +390,35 @@ int run_split(ep_ctx* c, const char* Q, const int64_t* qid, int64_t nq, const Sp
     return EP_OK;
 }
 
-// The same with the context's own buffers.
-int run_split_pass(ep_ctx* c, const int64_t* qid, int64_t nq, int* slices, int64_t* rows_pad,
-                   bool timed, bool capture) {
-    *rows_pad = round_up(std::max<int64_t>(nq, 1), kBM);
-    size_t kbytes = 0;
-    if (c->lt16 > kMaxFusedTiles) {
-        // one chunk's kernel values: at most 4 GiB, less where that does
-        // not fit (a chunk is as good as its launches are full)
-        kbytes = std::min((size_t)kvalue_bytes(nq, c->n), kValueBudget);
-        const size_t least = (size_t)kvalue_bytes(nq, kCPanel);
-        hipError_t e = c->kbuf.ensure(std::max(kbytes, least));
-        while (e == hipErrorOutOfMemory && kbytes > least) {
-            (void)hipGetLastError();
-            kbytes /= 2;
-            e = c->kbuf.ensure(std::max(kbytes, least));
+// Buffers and plan of the split pass over nq queries. Beyond kMaxFusedTiles
+// label tiles one chunk's kernel values take at most kValueBudget, less where
+// that does not fit (a chunk is as good as its launches are full).
+hipError_t split_room(ep_ctx* c, int64_t nq, SplitPlan* plan) {
+    const int64_t rows_pad = round_up(nq, kBM);
+    hipError_t e = c->Qp.ensure(packed_bytes(c, nq));
+    if (e != hipSuccess) return e;
+    const bool stored = c->lt16 > kMaxFusedTiles;
+    const size_t least = stored ? (size_t)kvalue_bytes(nq, kCPanel) : 0;
+    size_t kbytes = stored ? std::min((size_t)kvalue_bytes(nq, c->n), kValueBudget) : 0;
+    for (;;) {
+        kbytes = std::max(kbytes, least);
+        e = stored ? c->kbuf.ensure(kbytes) : hipSuccess;
+        if (e == hipSuccess) {
+            *plan = plan_split(c, nq, max_slices_for(rows_pad, c->l_pad, kMaxSplits), kbytes);
+            e = c->part.ensure((size_t)plan->splits * (size_t)rows_pad * c->l_pad * sizeof(float));
         }
-        HIP_TRY(e);
+        if (e != hipErrorOutOfMemory || kbytes == least) return e;
+        (void)hipGetLastError();
+        c->kbuf.release();
+        kbytes /= 2;
     }
-    const SplitPlan plan = plan_split(c, nq, max_slices_for(*rows_pad, c->l_pad, kMaxSplits), kbytes);
+}
+
+// The split pass with the context's own buffers (split_room).
+int run_split_pass(ep_ctx* c, const int64_t* qid, int64_t nq, const SplitPlan& plan, int* slices,
+                   int64_t* rows_pad, bool timed, bool capture) {
+    *rows_pad = round_up(nq, kBM);
     *slices = plan.splits;
-    HIP_TRY(c->part.ensure((size_t)plan.splits * (size_t)(*rows_pad) * c->l_pad * sizeof(float)));
     return run_split(c, c->Qp.as<char>(), qid, nq, plan, c->part.as<float>(), *rows_pad,
                      c->kbuf.as<char>(), timed, capture);
 }
@@ -431,11 +459,11 @@ int run_blocked(ep_ctx* c, const float* Q, int64_t ldq, const float* qn, const i
     *rows_pad = round_up(std::max<int64_t>(nq, 1), kBM);
     const int S = std::max(1, std::min(32, max_slices_for(*rows_pad, c->l_pad)));
     const int64_t kw = std::max<int64_t>(64, round_up(ceil_div(c->n, S), 64));
-    HIP_TRY(c->part.ensure((size_t)S * (*rows_pad) * c->l_pad * sizeof(float)));
+    HIP_TRY(need(c, c->part, (size_t)S * (*rows_pad) * c->l_pad * sizeof(float)));
     const int64_t rows256 = round_up(nq, 256);
     int64_t ldo = (int64_t)(c->block_bytes / ((size_t)rows256 * sizeof(float))) / 256 * 256;
     ldo = std::max<int64_t>(256, std::min<int64_t>(ldo, round_up(c->n, 256)));
-    HIP_TRY(c->kbuf.ensure((size_t)rows256 * ldo * sizeof(float)));
+    HIP_TRY(need(c, c->kbuf, (size_t)rows256 * ldo * sizeof(float)));
     if (int rc = ensure_blas(c)) return rc;
     const size_t slice_elems = (size_t)(*rows_pad) * c->l_pad;
     int rc = EP_OK;
@@ -493,12 +521,12 @@ int run_main_pass(ep_ctx* c, const float* Q, int64_t ldq, const float* qn, const
                    c->alpha.as<float>(), slices, rows_pad, timed, false, capture);
 }
 
-// Whether step 2 of a batch of m rows (gathered, row length d) captures the
-// subsample columns for steps 4-5: fused form, vector body, and the capture
-// buffer and the product's partial slices within budget.
-bool capture_subsample(const ep_ctx* c, const float* xb, int64_t m) {
-    if (c->k == 0 || use_blocked(c, xb, c->d)) return false;
-    return (use_split_step(c, m) || kmv_vec(xb, c->d, c->X, c->d, c->d)) &&
+// Whether step 2 of a batch of m rows captures the subsample columns for
+// steps 4-5: fused form, split pass or vector body (the gathered rows are
+// 16-byte aligned), and the capture buffer within budget.
+bool capture_subsample(const ep_ctx* c, int64_t m, bool split) {
+    if (c->k == 0 || use_blocked(c, nullptr, c->d)) return false;
+    return (split || kmv_vec(nullptr, c->d, c->X, c->d, c->d)) &&
            (size_t)c->s * (size_t)round_up(m, kBM) * sizeof(float) <= kKsbBudget;
 }
 
@@ -737,10 +765,7 @@ int setup_split(ep_ctx* c) {
     if (c->split && (c->Xp.ensure(xp) != hipSuccess || c->wplanes.ensure(wp) != hipSuccess ||
                      c->xinv.ensure((size_t)n * sizeof(float)) != hipSuccess ||
                      c->lolo.ensure((size_t)panels * sizeof(int)) != hipSuccess)) {
-        (void)hipGetLastError();       // another allocation took the memory meanwhile
-        c->Xp.release();
-        c->wplanes.release();
-        c->split = false;
+        drop_split(c);                 // another allocation took the memory meanwhile
     }
     if (!c->split) return EP_OK;
     HIP_TRY(launch_fill_f32(c->wplanes.as<float>(), (int64_t)(wp / 4), 0.f, st));
@@ -823,13 +848,14 @@ int do_setup(ep_ctx* c, const int64_t* sub_idx, uint64_t seed, const double* sig
                           hipMemcpyHostToDevice));
     }
     HIP_TRY(launch_row_norms(c->X, n, d, d, c->norms.as<float>(), st));
-    if (int rc = setup_split(c)) return rc;
     HIP_TRY(launch_gather_rows(c->X, n, d, c->norms.as<float>(), c->r_dev.as<int64_t>(), s,
                                c->s_pad, c->Xs.as<float>(), c->xs_norms.as<float>(),
                                c->err.as<int>(), st));
 
     int rc = sigma_in ? eigensystem_from_saved(c, sigma_in, V_in) : eigensystem_from_solver(c);
     if (rc) return rc;
+    // (after the eigensolver has given its workspaces back)
+    if ((rc = setup_split(c))) return rc;
 
     int herr = 0;
     HIP_TRY(hipMemcpyAsync(&herr, c->err.p, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -882,7 +908,7 @@ int subsample_correction(ep_ctx* c, bool capture, const float* xb, const float* 
         const ThinGemmPlan pl = thin_gemm_plan(M, N, K, groups, min_depth);
         const int64_t slice = M * ldo;
         const bool direct = pl.chunks == 1 && !Dk;
-        if (!direct) HIP_TRY(c->part.ensure((size_t)pl.chunks * slice * sizeof(float)));
+        if (!direct) HIP_TRY(need(c, c->part, (size_t)pl.chunks * slice * sizeof(float)));
         ThinGemmArgs g{};
         g.A = A;
         g.lda = lda;
@@ -901,18 +927,18 @@ int subsample_correction(ep_ctx* c, bool capture, const float* xb, const float* 
         return EP_OK;
     };
     int rc = EP_OK;
-    HIP_TRY(c->W1.ensure((size_t)k * L * sizeof(float)));
+    HIP_TRY(need(c, c->W1, (size_t)k * L * sizeof(float)));
     float* W = c->W1.as<float>();
     const double g_first = (double)s * m * L + (double)k * s * L;
     const double u_first = (double)k * s * m + (double)k * m * L;
     if (capture && u_first < g_first) {
-        HIP_TRY(c->G.ensure((size_t)k * ldk * sizeof(float)));
+        HIP_TRY(need(c, c->G, (size_t)k * ldk * sizeof(float)));
         float* U = c->G.as<float>();
         if ((rc = product(V, kld, true, c->ksb.as<float>(), ldk, k, m, s, nullptr, U, ldk)))
             return rc;
         if ((rc = product(U, ldk, false, R, L, k, L, m, c->Dk.as<float>(), W, L))) return rc;
     } else {
-        HIP_TRY(c->G.ensure((size_t)s * L * sizeof(float)));
+        HIP_TRY(need(c, c->G, (size_t)s * L * sizeof(float)));
         float* G = c->G.as<float>();
         if (capture) {
             if ((rc = product(c->ksb.as<float>(), ldk, false, R, L, s, L, m, nullptr, G, L)))
@@ -952,12 +978,28 @@ int subsample_correction(ep_ctx* c, bool capture, const float* xb, const float* 
     return EP_OK;
 }
 
-int ensure_step_buffers(ep_ctx* c, int64_t m) {
+// Which pass a step of m rows takes, and the buffers that it uses before
+// alpha changes. Without room for those of the split pass the split operands
+// are given up.
+int step_room(ep_ctx* c, int64_t m, bool* split, bool* capture, SplitPlan* plan) {
     const int64_t m_pad = round_up(m, kBN);
-    HIP_TRY(c->xb.ensure((size_t)m_pad * c->d * sizeof(float)));
-    HIP_TRY(c->xb_norms.ensure((size_t)m_pad * sizeof(float)));
-    HIP_TRY(c->R.ensure((size_t)m_pad * c->l_pad * sizeof(float) + kWeightTail));
-    return EP_OK;
+    for (;;) {
+        *split = use_split_step(c, m);
+        *capture = capture_subsample(c, m, *split);
+        if (*split) {
+            const hipError_t e = split_room(c, m, plan);
+            if (e == hipErrorOutOfMemory) {
+                drop_split(c);
+                continue;
+            }
+            HIP_TRY(e);
+        }
+        HIP_TRY(need(c, c->R, (size_t)m_pad * c->l_pad * sizeof(float) + kWeightTail));
+        HIP_TRY(need(c, c->xb, (size_t)m_pad * c->d * sizeof(float)));
+        HIP_TRY(need(c, c->xb_norms, (size_t)m_pad * sizeof(float)));
+        if (*capture) HIP_TRY(need(c, c->ksb, (size_t)c->s * round_up(m, kBM) * sizeof(float)));
+        if (!*split || c->split) return EP_OK;      // (else they were given up for one of these)
+    }
 }
 
 }  // namespace
@@ -1079,7 +1121,9 @@ int ep_step(ep_ctx* c, const int64_t* t, int64_t m, const float* y_b, float* f_o
             c->seen[th[i]] = 1;
         }
     }
-    int rc = ensure_step_buffers(c, m);
+    bool split = false, capture = false;
+    SplitPlan plan{};
+    int rc = step_room(c, m, &split, &capture, &plan);
     if (rc) return rc;
     if (c->timing) {
         rc = record(st, c->step_ev, true);
@@ -1091,14 +1135,9 @@ int ep_step(ep_ctx* c, const int64_t* t, int64_t m, const float* y_b, float* f_o
     float* alpha = c->alpha.as<float>();
     float* R = c->R.as<float>();
 
-    const bool capture = capture_subsample(c, xb, m);
-    const bool split = use_split_step(c, m);
     // step 1: gather the batch (the rows themselves only where a float32
     // pass reads them)
-    if (split) {
-        HIP_TRY(c->Qp.ensure(packed_bytes(c, m)));
-        if ((rc = pack_queries(c, c->X, t, m, c->Qp.as<char>(), true))) return rc;
-    }
+    if (split && (rc = pack_queries(c, c->X, t, m, c->Qp.as<char>(), true))) return rc;
     if (!split || (c->k > 0 && !capture))
         HIP_TRY(launch_gather_rows(c->X, c->n, c->d, c->norms.as<float>(), t, m, m_pad, xb, xbn,
                                    c->err.as<int>(), st));
@@ -1106,8 +1145,7 @@ int ep_step(ep_ctx* c, const int64_t* t, int64_t m, const float* y_b, float* f_o
     // subsample columns are kept for steps 4-5 when the buffer allows
     int slices = 0;
     int64_t rows_pad = 0;
-    if (capture) HIP_TRY(c->ksb.ensure((size_t)c->s * round_up(m, kBM) * sizeof(float)));
-    rc = split ? run_split_pass(c, t, m, &slices, &rows_pad, c->timing, capture)
+    rc = split ? run_split_pass(c, t, m, plan, &slices, &rows_pad, c->timing, capture)
                : run_main_pass(c, xb, c->d, xbn, t, m, &slices, &rows_pad, c->timing, capture);
     if (rc) return rc;
     // step 3: R = F - y_b; alpha_t -= c R
@@ -1134,15 +1172,12 @@ int ep_predict(ep_ctx* c, const float* Z, int64_t n_z, float* out) {
     if (!Z || !out) return fail(EP_EINVAL, "Z and out must be device pointers");
     DeviceGuard dg(c->device);
     hipStream_t st = c->stream;
-    const bool split = use_split(c, n_z);
+    bool split = use_split(c, n_z);
     int64_t chunk = 32768;
     if (split) {
         // packed rows of a chunk: at most 512 MiB, at least one panel
         const int64_t panels = (int64_t)(size_t(512) << 20) / panel_bytes(kQPanel, c->d);
         chunk = std::min(chunk, std::max<int64_t>(1, panels) * kQPanel);
-        HIP_TRY(c->Qp.ensure(packed_bytes(c, std::min(n_z, chunk))));
-    } else {
-        HIP_TRY(c->zn.ensure((size_t)std::min(n_z, chunk) * sizeof(float)));
     }
     for (int64_t z0 = 0; z0 < n_z; z0 += chunk) {
         const int64_t nz = std::min(chunk, n_z - z0);
@@ -1150,10 +1185,21 @@ int ep_predict(ep_ctx* c, const float* Z, int64_t n_z, float* out) {
         int slices = 0;
         int64_t rows_pad = 0;
         int rc = EP_OK;
+        SplitPlan plan{};
+        if (split) {
+            const hipError_t e = split_room(c, nz, &plan);
+            if (e == hipErrorOutOfMemory) {
+                drop_split(c);
+                split = false;
+            } else {
+                HIP_TRY(e);
+            }
+        }
         if (split) {
             if ((rc = pack_queries(c, Zc, nullptr, nz, c->Qp.as<char>(), false))) return rc;
-            rc = run_split_pass(c, nullptr, nz, &slices, &rows_pad, false, false);
+            rc = run_split_pass(c, nullptr, nz, plan, &slices, &rows_pad, false, false);
         } else {
+            HIP_TRY(need(c, c->zn, (size_t)nz * sizeof(float)));
             HIP_TRY(launch_row_norms(Zc, nz, c->d, c->d, c->zn.as<float>(), st));
             rc = run_main_pass(c, Zc, c->d, c->zn.as<float>(), nullptr, nz, &slices, &rows_pad,
                                false);
@@ -1363,19 +1409,26 @@ int ep_batch_sweep(ep_ctx* c, const int64_t* ms, int count, int reps, double* ms
         int slices = 0;
         int64_t rows_pad = 0;
         // the step-2 pass with the first m rows of X as the batch
+        bool split = use_split_step(c, m);
+        SplitPlan plan{};
+        if (split) {
+            const hipError_t e = split_room(c, m, &plan);
+            if (e == hipErrorOutOfMemory) {
+                drop_split(c);
+                split = false;
+            } else if (e != hipSuccess) {
+                rc = fail(EP_EDEVICE, "room for a batch of %lld rows: %s", (long long)m,
+                          hipGetErrorString(e));
+                break;
+            }
+        }
         auto pass = [&]() {
-            if (use_split_step(c, m)) return run_split_pass(c, nullptr, m, &slices, &rows_pad, false, false);
+            if (split) return run_split_pass(c, nullptr, m, plan, &slices, &rows_pad, false, false);
             return run_kmv(c, c->X, c->d, c->norms.as<float>(), nullptr, m, c->X, c->d,
                            c->norms.as<float>(), nullptr, c->n, c->alpha.as<float>(), &slices,
                            &rows_pad, false, false);
         };
-        if (use_split_step(c, m)) {
-            if (c->Qp.ensure(packed_bytes(c, m)) != hipSuccess)
-                rc = fail(EP_ENOMEM, "packed batch of %lld rows", (long long)m);
-            else
-                rc = pack_queries(c, c->X, nullptr, m, c->Qp.as<char>(), true);
-            if (rc) break;
-        }
+        if (split && (rc = pack_queries(c, c->X, nullptr, m, c->Qp.as<char>(), true))) break;
         rc = pass();
         if (rc) break;
         if (hipEventRecord(e0, c->stream) != hipSuccess) rc = fail(EP_EDEVICE, "event record");

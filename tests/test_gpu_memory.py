@@ -1,0 +1,130 @@
+"""Short device memory: the split operands (packed centres, planes of alpha)
+are optional. A setup that has no room for them beside its own work, and calls
+whose buffers no longer fit beside them, run on float32 operands instead of
+failing. The rest of the device is held by one tensor meanwhile; some hundred
+megabytes always stay free for the runtime."""
+
+import numpy as np
+import pytest
+
+from gpu_common import TOL_STEP, rel
+
+GB = 1 << 30
+
+
+class Hold:
+    """A tensor over all free memory but `leave` bytes."""
+
+    def __init__(self, torch, leave):
+        self.torch = torch
+        torch.cuda.empty_cache()
+        free, _ = torch.cuda.mem_get_info()
+        assert free > leave
+        self.t = torch.empty(free - leave, dtype=torch.uint8, device="cuda")
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, *a):
+        self.t = None
+        self.torch.cuda.empty_cache()
+
+
+def _free(torch):
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def _predict(ep, torch, ctx, Z, l):
+    out = torch.empty((Z.shape[0], l), device="cuda")
+    ep.ep_predict(ctx, Z, Z.shape[0], out)
+    ep.ep_sync(ctx)
+    return out.cpu().numpy()
+
+
+@pytest.fixture(scope="module")
+def problem():
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    n, d, l = 65536, 8192, 16          # packed centres: 2.1 GB
+    X = torch.randn((n, d), device="cuda", generator=gen)
+    Z = torch.randn((16500, d), device="cuda", generator=gen)
+    a = torch.randn((n, l), device="cuda", generator=gen)
+    yield torch, X, Z, a, n, d, l, 40.0      # (typical kernel values 0.006)
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+def test_setup_and_calls_without_room(problem):
+    torch, X, Z, a, n, d, l, bw = problem
+    import paper_1806_06144_amd as ep
+    r = np.arange(0, 30000, 100)
+    t = torch.arange(1000, 1700, device="cuda")
+    y = torch.zeros((700, l), device="cuda")
+
+    def calls(ctx):
+        ep.ep_set_alpha(ctx, a)
+        f = torch.empty((700, l), device="cuda")
+        ep.ep_step(ctx, t, 700, y, f)
+        P = _predict(ep, torch, ctx, Z[:600].contiguous(), l)
+        A = torch.empty((n, l), device="cuda")
+        ep.ep_get_alpha(ctx, A)
+        ep.ep_sync(ctx)
+        return f.cpu().numpy(), P, (A - a).cpu().numpy()
+
+    before = _free(torch)
+    ctx, _ = ep.ep_setup(X, n, d, l, "gaussian", bw, len(r), 20, sub_idx=r)
+    assert before - _free(torch) > 2 * GB             # the packed centres are held
+    want = calls(ctx)
+    ep.ep_destroy(ctx)
+    with Hold(torch, 3 * GB):                         # half of it is less than they need
+        before = _free(torch)
+        ctx, _ = ep.ep_setup(X, n, d, l, "gaussian", bw, len(r), 20, sub_idx=r)
+        try:
+            assert before - _free(torch) < GB // 2
+            got = calls(ctx)
+        finally:
+            ep.ep_destroy(ctx)
+    for g, w in zip(got, want):
+        assert rel(g, w) < TOL_STEP
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+def test_split_operands_are_given_up_for_a_call(problem):
+    torch, X, Z, a, n, d, l, bw = problem
+    import paper_1806_06144_amd as ep
+    r = np.arange(0, 30000, 100)
+    with Hold(torch, 6 * GB):
+        ctx, _ = ep.ep_setup(X, n, d, l, "gaussian", bw, len(r), 20, sub_idx=r)
+        try:
+            ep.ep_set_alpha(ctx, a)
+            want = _predict(ep, torch, ctx, Z[:600].contiguous(), l)
+            with Hold(torch, GB // 3):                # packed queries: 0.5 GB
+                before = _free(torch)
+                P = _predict(ep, torch, ctx, Z, l)
+                assert _free(torch) - before > GB     # the packed centres went
+                assert rel(P[:600], want) < TOL_STEP
+                ep.ep_set_alpha(ctx, -a)              # (alpha itself stays in use)
+                P2 = _predict(ep, torch, ctx, Z[:600].contiguous(), l)
+                ep.ep_set_alpha(ctx, a)
+            P1 = _predict(ep, torch, ctx, Z[:600].contiguous(), l)
+        finally:
+            ep.ep_destroy(ctx)
+    assert rel(P1, want) < TOL_STEP and rel(-P2, want) < TOL_STEP
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+def test_the_eigensolver_comes_first(problem):
+    """K_s of 20000 rows (3.0 GB) and their features (0.6) fit; beside the
+    packed centres (2.0, less than half of what the features leave) K_s does
+    not."""
+    torch, X, Z, a, n, d, l, bw = problem
+    import paper_1806_06144_amd as ep
+    with Hold(torch, 5 * GB):
+        ctx, info = ep.ep_setup(X, n, d, l, "gaussian", bw, 20000, 10,
+                                sub_idx=np.arange(0, 40000, 2))
+        ep.ep_destroy(ctx)
+    assert info.sigma_1 > info.sigma_k1 > 0
