@@ -792,9 +792,7 @@ SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, bool ll, int 
     SplitPlan best{1, nt, 0.0};
     best.cw = cw;
     double bt = 1e300;
-    for (int64_t P = 1; P <= nt && P <= max_slices; ++P) {
-        const int64_t per = ceil_div(nt, P);
-        if (ceil_div(nt, per) != P) continue;
+    each_split(nt, max_slices, [&](int64_t P, int64_t per) {
         const double t = (double)ceil_div(tq * P, slots) * ((double)per + 0.5);
         if (t < bt) {
             bt = t;
@@ -802,7 +800,7 @@ SplitPlan split_plan(int64_t nq, int64_t nc, int64_t lt, int kind, bool ll, int 
             best.tps = per;
             best.cost = t;
         }
-    }
+    });
     return best;
 }
 
@@ -816,9 +814,7 @@ SplitPlan wmul_plan(int64_t nq, int64_t groups, int64_t lt, int max_slices) {
     const int64_t quads = ceil_div(std::max<int64_t>(groups, 1), 4);
     SplitPlan best{1, 4 * quads, 0.0};
     double bt = 1e300;
-    for (int64_t P = 1; P <= quads && P <= max_slices; ++P) {
-        const int64_t per = ceil_div(quads, P);
-        if (ceil_div(quads, per) != P) continue;
+    each_split(quads, max_slices, [&](int64_t P, int64_t per) {
         // (partial sums in and out cost about two groups' products)
         const double t = (double)ceil_div(tiles * P, slots) * (4.0 * (double)per + 2.0);
         if (t < bt) {
@@ -827,7 +823,7 @@ SplitPlan wmul_plan(int64_t nq, int64_t groups, int64_t lt, int max_slices) {
             best.tps = 4 * per;
             best.cost = t;
         }
-    }
+    });
     return best;
 }
 

@@ -58,6 +58,41 @@ def test_their_launches_are_capped_and_walk(name, file):
     assert "+= " in body[:900] and "gridDim.x" in body[:900]
 
 
+SPLITS = r"""
+#include "launch.h"
+#include <cmath>
+#include <cstdio>
+#include <vector>
+typedef std::vector<std::pair<int64_t, int64_t>> List;
+int main() {
+    for (int64_t items = 1; items < 70000; items += items < 700 ? 1 : 997)
+        for (int64_t most : {int64_t(1), int64_t(7), int64_t(512), int64_t(1) << 20}) {
+            List a, b;
+            ep::each_split(items, most, [&](int64_t p, int64_t per) { a.push_back({p, per}); });
+            for (int64_t p = 1; p <= items && p <= most; ++p) {
+                const int64_t per = (items + p - 1) / p;
+                if ((items + per - 1) / per == p) b.push_back({p, per});
+            }
+            if (a != b || (double)a.size() > 2 * std::sqrt((double)items) + 1) {
+                std::printf("items %lld most %lld: %zu and %zu\n", (long long)items,
+                            (long long)most, a.size(), b.size());
+                return 1;
+            }
+        }
+}
+"""
+
+
+def test_split_counts_are_those_of_a_full_scan(tmp_path):
+    src, exe = tmp_path / "s.cpp", tmp_path / "s"
+    src.write_text(SPLITS)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+    text = open(os.path.join(CSRC, "skmv.hip")).read()
+    assert text.count("each_split(") == 2 and "++P" not in text
+
+
 @pytest.mark.gpu
 @pytest.mark.timeout(300)
 def test_model_of_more_plane_dwords_than_threads():
