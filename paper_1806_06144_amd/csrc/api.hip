@@ -995,8 +995,10 @@ int step_room(ep_ctx* c, int64_t m, bool* split, bool* capture, SplitPlan* plan)
             HIP_TRY(e);
         }
         HIP_TRY(need(c, c->R, (size_t)m_pad * c->l_pad * sizeof(float) + kWeightTail));
-        HIP_TRY(need(c, c->xb, (size_t)m_pad * c->d * sizeof(float)));
-        HIP_TRY(need(c, c->xb_norms, (size_t)m_pad * sizeof(float)));
+        if (!*split || (c->k > 0 && !*capture)) {   // (a float32 pass reads the batch)
+            HIP_TRY(need(c, c->xb, (size_t)m_pad * c->d * sizeof(float)));
+            HIP_TRY(need(c, c->xb_norms, (size_t)m_pad * sizeof(float)));
+        }
         if (*capture) HIP_TRY(need(c, c->ksb, (size_t)c->s * round_up(m, kBM) * sizeof(float)));
         if (!*split || c->split) return EP_OK;      // (else they were given up for one of these)
     }
