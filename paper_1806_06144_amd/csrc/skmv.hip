@@ -180,14 +180,36 @@ __global__ void __launch_bounds__(1024) pack_rows_kernel(PackArgs p) {
     }
 }
 
-// Planes of a whole weight matrix (rows x l floats, leading dimension ldw).
+// Planes of a whole weight matrix (rows x l floats, leading dimension ldw),
+// labels up to lt tiles and rows up to whole groups of 32 zero. A thread packs
+// the eight weights of a lane of an operand (weight_elem), so that stores are
+// 16 bytes beside each other: 1.28 M x 1000 in 2.6 ms (5.1 GB in, 7.7 out, 4.9
+// TB/s); one thread a weight, 2-byte stores 16 bytes apart, took 12.5.
 __global__ void __launch_bounds__(256) pack_weights_kernel(const float* W, int64_t rows, int64_t l,
                                                            int64_t ldw, int64_t lt,
                                                            unsigned short* planes) {
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < rows * l;
+    typedef unsigned short ushortx8 __attribute__((ext_vector_type(8)));
+    const int64_t lanes = (rows + 31) / 32 * lt * 64;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < lanes;
          e += (int64_t)gridDim.x * 256) {
-        const int64_t c = e / l, j = e - c * l;
-        store_weight(planes, weight_elem(c, j, lt), W[c * ldw + j]);
+        const int lane = (int)(e & 63);
+        const int64_t frag = e >> 6, group = frag / lt;
+        const int64_t j = 16 * (frag - group * lt) + (lane & 15);
+        const int64_t c0 = 32 * group + 4 * (lane >> 4);
+        ushortx8 h, m, o;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int64_t c = c0 + 16 * (i >> 2) + (i & 3);
+            unsigned short a, b, d;
+            split_weight(c < rows && j < l ? W[c * ldw + j] : 0.f, a, b, d);
+            h[i] = a;
+            m[i] = b;
+            o[i] = d;
+        }
+        ushortx8* at = reinterpret_cast<ushortx8*>(planes) + frag * 3 * 64 + lane;
+        at[0] = h;
+        at[64] = m;
+        at[128] = o;
     }
 }
 
@@ -776,8 +798,9 @@ hipError_t launch_pack_rows(PackArgs a, hipStream_t s) {
 hipError_t launch_pack_weights(const float* W, int64_t rows, int64_t l, int64_t ldw, int64_t lt,
                                void* planes, hipStream_t s) {
     if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(pack_weights_kernel, dim3(stride_grid(ceil_div(rows * l, 256), 256)), dim3(256),
-                       0, s, W, rows, l, ldw, lt, static_cast<unsigned short*>(planes));
+    const int64_t lanes = ceil_div(rows, 32) * lt * 64;
+    hipLaunchKernelGGL(pack_weights_kernel, dim3(stride_grid(ceil_div(lanes, 256), 256)), dim3(256), 0,
+                       s, W, rows, l, ldw, lt, static_cast<unsigned short*>(planes));
     return hipGetLastError();
 }
 

@@ -115,11 +115,12 @@ __device__ __forceinline__ int64_t weight_elem(int64_t c, int64_t j, int64_t lt)
 inline __host__ __device__ int64_t weight_plane_bytes(int64_t n_pad, int64_t lt) {
     return (n_pad / 32) * lt * 3 * kFragBytes;
 }
-// Stores the three planes of one weight. Values that round up to infinity
-// in bf16 keep their largest finite head. Infinities and NaN go into the low
-// plane, which meets only the heads of kernel values: a head times infinity is
+// The three planes of one weight. Values that round up to infinity in bf16
+// keep their largest finite head. Infinities and NaN go into the low plane,
+// which meets only the heads of kernel values: a head times infinity is
 // infinite, as in float32, where a zero mid or low plane would make it NaN.
-__device__ __forceinline__ void store_weight(unsigned short* planes, int64_t at, float w) {
+__device__ __forceinline__ void split_weight(float w, unsigned short& hi, unsigned short& mid,
+                                             unsigned short& lo) {
     unsigned h = 0, m = 0, l = 0;
     if (__builtin_isfinite(w)) {
         h = pack_bf16(w, 0.f) & 0xffffu;
@@ -131,9 +132,12 @@ __device__ __forceinline__ void store_weight(unsigned short* planes, int64_t at,
     } else {
         l = pack_bf16(w, 0.f) & 0xffffu;
     }
-    planes[at] = (unsigned short)h;
-    planes[at + 512] = (unsigned short)m;
-    planes[at + 1024] = (unsigned short)l;
+    hi = (unsigned short)h;
+    mid = (unsigned short)m;
+    lo = (unsigned short)l;
+}
+__device__ __forceinline__ void store_weight(unsigned short* planes, int64_t at, float w) {
+    split_weight(w, planes[at], planes[at + 512], planes[at + 1024]);
 }
 
 }  // namespace ep
