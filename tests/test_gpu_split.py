@@ -322,3 +322,110 @@ def test_features_beyond_the_float32_squares(kernel):
     ref = oracle.predict(X[a[:, 6] != 0].astype(np.float64), a[a[:, 6] != 0][:, 6:7].astype(np.float64),
                          Z[rows].astype(np.float64), kernel_id(kernel), bw)
     assert rel(P[rows][:, 6:7], ref) < TOL_STEP
+
+
+# ---- the contraction's six products ------------------------------------------
+#
+# Distances of small integers are exact, so a kernel value is known to a few
+# roundings, and with one nonzero weight to a label the result is one product:
+# an error of 2^-17 in it, the size of the smallest of the six, shows.
+
+CONTRACTIONS = [
+    # l, n_z, ep_predict_noalloc (its kernel values come in several chunks
+    # beyond 160 labels): one label tile to ten, queries shared by the waves or not
+    (16, 1, False), (16, 100, False), (16, 300, False), (40, 40, False), (160, 30, False),
+    (160, 300, False), (161, 20, False), (300, 300, False), (300, 300, True), (1100, 129, False),
+]
+
+
+def _contraction_problem(l):
+    n, d = 128 * 300 + 5, 64
+    rng = np.random.default_rng(l)
+    X = rng.integers(-2, 3, (n, d)).astype(np.float32)
+    X[128 * 7:128 * 8] = X[:128]             # (kernel values up to 1)
+    at = (np.arange(l) * 9973 + 17) % n      # the centre of each label's weight
+    w = (rng.uniform(1, 2, l) * np.exp2(rng.integers(-12, 13, l)) * rng.choice([-1, 1], l)).astype(np.float32)
+    return n, d, X, at, w, bw32(10.0)
+
+
+def _exact_kernel(X, Z, bw):
+    scale = np.float64(np.float32(-np.log2(np.e) / (2 * bw * bw)))
+    Xd, Zd = X.astype(np.float64), Z.astype(np.float64)
+    d2 = (Zd ** 2).sum(1)[:, None] + (Xd ** 2).sum(1)[None] - 2 * Zd @ Xd.T
+    return np.exp2(scale * d2)
+
+
+# one product: the last addition truncated (2 eps), three products below 2^-26
+# left out; a sum of five adds a rounding each
+ONE, FIVE = 4 * EPS, 8 * EPS
+# a kernel value: exp2 good to 2 eps, its argument (at most 4) rounded
+VALUE = (2 + 4 * np.log(2) + 1) * EPS
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("l,n_z,noalloc", CONTRACTIONS)
+def test_every_product_of_the_contraction(l, n_z, noalloc):
+    import paper_1806_06144_amd as ep
+    n, d, X, at, w, bw = _contraction_problem(l)
+    rng = np.random.default_rng(n_z)
+    Z = X[rng.integers(0, n, n_z)].copy()
+    Z[:, :40] = X[at[np.arange(n_z) % l], :40]
+    assert -(-n_z // 64) * 64 * n * d > 2 ** 27
+
+    with Gpu(X, l, "gaussian", bw, 20, 2, np.arange(20)) as g:
+        def predict(a):
+            g.set_alpha(a)
+            out = g.torch.full((n_z, l), float("nan"), device=g.dev)
+            call = ep.ep_predict_noalloc if noalloc else ep.ep_predict
+            call(g.ctx, g.t(Z), n_z, out)
+            ep.ep_sync(g.ctx)
+            return out.cpu().numpy().astype(np.float64)
+
+        a = np.zeros((n, l), dtype=np.float32)
+        a[at, np.arange(l)] = 1.0
+        K = predict(a)                       # head of the weight, all planes of the values
+        K_o = _exact_kernel(X[at], Z, bw)
+        assert K.max() > 0.3 and np.max(np.abs(K - K_o) / K_o) <= VALUE
+        a[at, np.arange(l)] = w
+        F = predict(a)
+        assert np.max(np.abs(F - K * w) / (K * np.abs(w))) <= ONE
+        # five centres of one group of 32 to a label
+        a[:] = 0.0
+        five = at[:, None] // 32 * 32 + (at[:, None] + 7 * np.arange(5)) % 32
+        five = np.minimum(five, n - 1)
+        ws = w[:, None] * np.float32([1.0, 0.3, -0.7, 0.11, 0.9])
+        for i in range(5):
+            np.add.at(a, (five[:, i], np.arange(l)), ws[:, i].astype(np.float32))
+        F = predict(a)
+    some = np.linspace(0, l - 1, min(l, 40)).astype(int)
+    for j in some:
+        rows = np.unique(five[j])
+        Kj = _exact_kernel(X[rows], Z, bw)
+        aj = a[rows, j].astype(np.float64)
+        assert np.max(np.abs(F[:, j] - Kj @ aj) / (Kj @ np.abs(aj))) <= FIVE + VALUE
+
+
+def _bf16(x):
+    u = np.asarray(x, dtype=np.float32).view(np.uint32)
+    return ((u + 0x7FFF + ((u >> 16) & 1)) & np.uint32(0xFFFF0000)).view(np.float32)
+
+
+@pytest.mark.parametrize("drop", [None] + [(i, j) for i in range(3) for j in range(3) if i + j <= 2])
+def test_the_bound_shows_a_missing_product(drop):
+    """The planes modelled in numpy: the bound above holds with the six
+    products and fails with any one of them left out."""
+    n, d, X, at, w, bw = _contraction_problem(161)
+    Z = X[np.random.default_rng(1).integers(0, n, 200)]
+    K = _exact_kernel(X[at], Z, bw).astype(np.float32)
+
+    def planes(x):
+        h = _bf16(x)
+        m = _bf16(x - h)
+        return h, m, _bf16(x - h - m)
+
+    kp, wp = planes(K), planes(w)
+    assert np.array_equal(kp[0] + kp[1] + kp[2], K) and np.array_equal(wp[0] + wp[1] + wp[2], w)
+    F = sum(kp[j].astype(np.float64) * wp[i] for i in range(3) for j in range(3)
+            if i + j <= 2 and (i, j) != drop)
+    worst = np.max(np.abs(F - K.astype(np.float64) * w) / (K * np.abs(w).astype(np.float64)))
+    assert (worst <= ONE) == (drop is None), worst / EPS
