@@ -893,13 +893,15 @@ int subsample_correction(ep_ctx* c, bool capture, const float* xb, const float* 
     const int64_t s = c->s, k = c->k, L = c->l_pad, kld = c->k_ld;
     const int64_t ldk = round_up(m, kBM);
     const int groups = 1024;
-    // Short products take chunks of one accumulation block (64): a tiny step
-    // (s = 500, m = 256) spends 41 us in them with chunks of 256, 17 us so.
-    // Where s m > 2^21 the products are long enough to fill the chip either
-    // way (15 us of 480 at s = 4000, m = 1310) and the chunks, which fix the
-    // order of summation, stay: the sums over the top eigenvector cancel, and
-    // their rounding is what a second step's result shows most.
-    const int64_t min_depth = keeps_order(c, m) || s * m > (int64_t(1) << 21) ? 256 : 64;
+    // Products in chunks of one accumulation block (64), so that short ones
+    // fill the chip: a tiny step (s = 500, m = 256) spends 41 us in them with
+    // chunks of 256, 17 us so, an MNIST-shaped one 447 and 434 us in all. The
+    // chunks' sums are added in float64: along the top eigenvector all terms
+    // have one sign, and what a later step sees is what is left when these sums
+    // cancel. Error of a run's second step (test_gpu_split.py) in units of what
+    // that amplifies: 2.0 with either length summed in float32, 1.2 so.
+    const bool order = keeps_order(c, m);
+    const int64_t min_depth = order ? 256 : 64;
     const float* V = c->V.as<float>();
     // partial slices of one product into c->part, summed (and scaled) into out
     auto product = [&](const float* A, int64_t lda, bool a_t, const float* B, int64_t ldb,
@@ -923,7 +925,7 @@ int subsample_correction(ep_ctx* c, bool capture, const float* xb, const float* 
         HIP_TRY(thin_gemm_launch(g, pl, a_t, false, st));
         if (!direct)
             HIP_TRY(launch_sum_slices(c->part.as<float>(), pl.chunks, slice, M, N, ldo, Dk, out,
-                                      ldo, st));
+                                      ldo, !order, st));
         return EP_OK;
     };
     int rc = EP_OK;

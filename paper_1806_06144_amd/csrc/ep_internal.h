@@ -238,10 +238,10 @@ ThinGemmPlan thin_gemm_plan(int64_t M, int64_t N, int64_t K, int min_groups, int
 hipError_t thin_gemm_launch(const ThinGemmArgs& a, const ThinGemmPlan& pl, bool a_t, bool scatter,
                             hipStream_t st);
 // out[i, j] = Dk[i] * sum_p part[p slice + i ld + j] (no scale when Dk is
-// NULL), for i < rows, j < cols; slices summed in order.
+// NULL), for i < rows, j < cols; slices summed in order, in float64 with f64.
 hipError_t launch_sum_slices(const float* part, int slices, int64_t slice, int64_t rows,
                              int64_t cols, int64_t ld, const float* Dk, float* out, int64_t ldo,
-                             hipStream_t st);
+                             bool f64, hipStream_t st);
 
 // Auxiliary kernels (kernels.hip).
 hipError_t launch_row_norms(const float* X, int64_t rows, int64_t d, int64_t ld,

@@ -182,6 +182,7 @@ __global__ void __launch_bounds__(kGThreads) thin_gemm_kernel(ThinGemmArgs p) {
 
 // out[i, j] = scale_i * sum_p part[p][i, j] (scale = 1 without Dk), slices
 // summed in order.
+template <class T>
 __global__ void __launch_bounds__(256) sum_slices_kernel(const float* part, int slices,
                                                          int64_t slice, int64_t rows, int64_t cols,
                                                          int64_t ld, const float* Dk, float* out,
@@ -190,7 +191,7 @@ __global__ void __launch_bounds__(256) sum_slices_kernel(const float* part, int 
     if (e >= rows * cols) return;
     const int64_t i = e / cols, j = e - i * cols;
     const float* at = part + i * ld + j;
-    float f = 0.f;
+    T f = 0;
     int s = 0;
     for (; s + 8 <= slices; s += 8) {           // eight loads in flight
         float v[8];
@@ -200,7 +201,7 @@ __global__ void __launch_bounds__(256) sum_slices_kernel(const float* part, int 
         for (int x = 0; x < 8; ++x) f += v[x];
     }
     for (; s < slices; ++s) f += at[(int64_t)s * slice];
-    out[i * ldo + j] = Dk ? Dk[i] * f : f;
+    out[i * ldo + j] = (float)(Dk ? Dk[i] * f : f);
 }
 
 }  // namespace
@@ -243,11 +244,12 @@ hipError_t thin_gemm_launch(const ThinGemmArgs& a, const ThinGemmPlan& pl, bool 
 
 hipError_t launch_sum_slices(const float* part, int slices, int64_t slice, int64_t rows,
                              int64_t cols, int64_t ld, const float* Dk, float* out, int64_t ldo,
-                             hipStream_t st) {
+                             bool f64, hipStream_t st) {
     if (rows <= 0 || cols <= 0) return hipSuccess;
     const int64_t count = rows * cols;
-    hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)ceil_div(count, 256)), dim3(256), 0, st,
-                       part, slices, slice, rows, cols, ld, Dk, out, ldo);
+    hipLaunchKernelGGL(f64 ? sum_slices_kernel<double> : sum_slices_kernel<float>,
+                       dim3((unsigned)ceil_div(count, 256)), dim3(256), 0, st, part, slices, slice,
+                       rows, cols, ld, Dk, out, ldo);
     return hipGetLastError();
 }
 
