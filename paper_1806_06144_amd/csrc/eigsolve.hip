@@ -107,12 +107,11 @@ __global__ void __launch_bounds__(256) reverse_pairs_kernel(const double* W, con
 // owns 64 x 64 of the result, a wave 32 x 16 as two blocks of
 // v_mfma_f64_16x16x4f64; stages of 32 depth pass through two LDS buffers,
 // loaded into registers two stages ahead (a stage's products are shorter than
-// a load from memory). The column tiles
-// of a block row share its part of K, so they run on one XCD (workgroups go
+// a load from memory). The column tiles of a block row share its part of K, so they run on one XCD (workgroups go
 // to the 8 XCDs round robin). s = 4000, 208 columns: 0.20 ms, 33 TFLOP/s,
 // bound by the waits between its stages, not by memory (a library kernel 0.44
-// ms); error 3.9e-16 of the result, the library's 1.9e-15. No load needs more than 8-byte alignment: s may
-// be odd.
+// ms); error 3.9e-16 of the result, the library's 1.9e-15. No load needs more
+// than 8-byte alignment: s may be odd.
 constexpr int kET = 64, kEK = 32, kEThreads = 512;
 
 __global__ void __launch_bounds__(kEThreads) symm_product_kernel(const double* K, const double* Y,
@@ -270,12 +269,17 @@ int subspace_topq(const double* K, int64_t s, int64_t q, const EigOpts& o, uint6
 
     auto product = [&](const double* Y, int64_t cols, double* out) {
         matvecs += cols;
-        // Between these sizes the library's tiles leave most of the chip idle
-        // over one long chain of depth; below it splits the depth, above its
-        // larger tiles win. 208 columns, own against library kernel: s = 3200
-        // 0.16 / 0.10 ms (140 columns), 4000 0.20 / 0.44, 6000 0.49 / 0.66,
-        // 8000 0.64 / 0.87, 12000 1.46 / 1.31.
-        if (s > 3584 && s <= 10240) {
+        // From s = 3768 (320 columns), 3792 (208) or 3824 (48) on the library's
+        // tiles leave most of the chip idle over one long chain of depth (below
+        // it splits the depth). The own kernel's time grows by whole rounds of
+        // workgroups, two to each of 256 CUs: within one round it is the faster,
+        // beyond it the library is. 208 columns, own against library kernel in
+        // ms: s = 3788 0.20 / 0.13, 3792 0.20 / 0.42, 4000 0.21 / 0.44, 6000 0.50
+        // / 0.65, 8192 (512 workgroups) 0.70 / 0.89, 8193 1.02 / 0.90, 10240 1.31
+        // / 1.12; 128 columns: 9216 0.77 / 1.00, 16000 (500) 1.34 / 1.74, 20000
+        // 2.57 / 2.19; 60 columns: 3808 0.19 / 0.12, 3824 0.19 / 0.42, 20000
+        // (313) 1.65 / 2.18.
+        if (s > 3790 && ceil_div(s, kET) * ceil_div(cols, kET) <= 512) {
             HIP_TRY(launch_symm_product(K, Y, s, cols, out, st));
             return (int)EP_OK;
         }

@@ -156,3 +156,32 @@ def test_subspace_product_edges(s, k):
     den = _setup(X, cfg, r, solver="dense")
     assert sub[0].solver == SUBSPACE and sub[0].eig_residual <= 1e-11
     _agree(sub, den)
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("s,k", [(3790, 20), (3791, 20), (3839, 95), (3904, 3), (6001, 60),
+                                 (8192, 170), (8193, 170), (10300, 100), (12001, 20)])
+def test_subspace_product_range(s, k):
+    """Both sides of the lines between the filter's own product and the
+    library's (s = 3790; 512 tiles of 64 x 64), and sizes inside: eigenvalues
+    against the Rayleigh quotients of the returned vectors with a K_s of
+    torch's, whose error is the square of the vectors' (6e-8 from float32)."""
+    import torch
+    import paper_1806_06144_amd as ep
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(s)
+    n, d, bw = s + 100, 40, 2.0
+    X = torch.rand((n, d), device="cuda", generator=gen)
+    opts = ep.EpSetupOpts(solver=SUBSPACE, no_fallback=1)
+    ctx, info = ep.ep_setup_ex(X, n, d, 1, "gaussian", bw, s, k, sub_idx=np.arange(s), opts=opts)
+    sigma, _, V, _ = ep.ep_get_preconditioner(ctx, info)
+    ep.ep_destroy(ctx)
+    assert info.solver == SUBSPACE and info.eig_residual <= 1e-11
+    x = X[:s].double()
+    K = (x * x).sum(1)[:, None] + (x * x).sum(1)[None] - 2.0 * torch.matmul(x, x.T.contiguous())
+    K = torch.exp(K.clamp_(min=0.0) / (-2.0 * bw * bw))
+    K.fill_diagonal_(1.0)
+    V = torch.from_numpy(np.asarray(V).reshape(s, k)).cuda().double()
+    ray = ((V * torch.matmul(K, V)).sum(0) / (V * V).sum(0)).cpu().numpy()
+    assert np.max(np.abs(ray - np.asarray(sigma)[:k])) <= 1e-11 * info.sigma_1
