@@ -41,17 +41,6 @@ KERNEL_SOURCES = {"kmv_kernel": ["kmv.hip", "ep_device.h"],
                   "kblock_kernel": ["kblock.hip", "ep_device.h"]}
 
 
-def split_step(n, d, l, kernel, m):
-    """Whether a fused training step runs on the 16-bit matrix cores (the
-    library's use_split_step, where its packed operands fit the device)."""
-    tiles = -(-l // 16)
-    if kernel == "laplacian" and d > 2048:
-        return False
-    if tiles > 10 and (m > 2048 or m * n > 1 << 29):
-        return False
-    return -(-m // 64) * 64 * n * d > 1 << 27
-
-
 def code_text(src):
     """C++ source with its comments removed and blank space collapsed, so
     that a measurement stays attached to the code it measured when only
@@ -674,6 +663,7 @@ def main():
     ep.ep_sync(ctx)
     tim = ep.ep_timing_read(ctx)
     ep.ep_timing_enable(ctx, False)
+    step_pass = ep.ep_step_pass(ctx, m)
     step_ms = [evs[i].elapsed_time(evs[i + 1]) for i in range(args.steps)]
 
     # the short last batch of an epoch (n mod m rows), for the epoch time
@@ -774,8 +764,9 @@ def main():
         dom_avg_s = kmv_avg_s
         dom_flops = kmv_flops
         gemm_tflops = None
-        if args.contraction != "blocked" and split_step(n, d, l, cfg.kernel, m):
-            # three fp16 products per feature, six bf16 products per label
+        if step_pass == ep.EP_PASS_SPLIT:
+            # three fp16 products per feature (four for a panel of centres
+            # that needs them), six bf16 products per label
             dom = "skmv_kernel"
             dom_label = "skmv_kernel (step 2 on the 16-bit matrix cores: 3 d + 6 l products per entry)"
             dom_flops = 2.0 * m * n * (3 * d + 6 * l)

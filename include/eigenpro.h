@@ -333,6 +333,17 @@ enum { EP_CONTRACT_AUTO = 0, EP_CONTRACT_FUSED = 1, EP_CONTRACT_BLOCKED = 2 };
  * Errors: EP_EINVAL for an unknown mode or negative block_bytes. */
 int ep_set_contraction(ep_ctx* ctx, int mode, int64_t block_bytes);
 
+/* The matrix units on which ep_step forms F for a batch of m rows, as the
+ * context stands (contraction form, operands held, sizes); rooflines and
+ * comparisons of precision need it. A later call may give the split operands
+ * up (see ep_setup). Errors: EP_EINVAL (NULL, m outside [1, n]). */
+enum {
+    EP_PASS_FLOAT32 = 0,   /* fused pass on float32 operands                   */
+    EP_PASS_SPLIT = 1,     /* 16-bit matrix cores, split operands              */
+    EP_PASS_BLOCKED = 2    /* blocked form                                     */
+};
+int ep_step_pass(ep_ctx* ctx, int64_t m, int* pass);
+
 /* Device probe (no context): runs a register-only kernel of independent
  * fp32 MFMA chains (v_mfma_f32_32x32x2f32, two waves per SIMD on every CU)
  * on the current device and default stream, and reports the rate it

@@ -23,6 +23,7 @@ EP_SOLVER_AUTO, EP_SOLVER_DENSE, EP_SOLVER_SUBSPACE = 0, 1, 2
 EP_CONTRACT_AUTO, EP_CONTRACT_FUSED, EP_CONTRACT_BLOCKED = 0, 1, 2
 CONTRACTIONS = {"auto": EP_CONTRACT_AUTO, "fused": EP_CONTRACT_FUSED,
                 "blocked": EP_CONTRACT_BLOCKED}
+EP_PASS_FLOAT32, EP_PASS_SPLIT, EP_PASS_BLOCKED = 0, 1, 2
 SOLVERS = {"auto": EP_SOLVER_AUTO, "dense": EP_SOLVER_DENSE, "subspace": EP_SOLVER_SUBSPACE}
 KERNELS = {"gaussian": EP_GAUSSIAN, "laplacian": EP_LAPLACIAN}
 _CODES = {EP_EINVAL: "EP_EINVAL", EP_ENOMEM: "EP_ENOMEM", EP_EDEVICE: "EP_EDEVICE",
@@ -91,6 +92,7 @@ def _load():
         "ep_set_checks": (I, [P, I]),
         "ep_set_rank": (I, [P, I64]),
         "ep_set_contraction": (I, [P, I, I64]),
+        "ep_step_pass": (I, [P, I64, ctypes.POINTER(I)]),
         "ep_adapt": (I, [P, I64, ctypes.POINTER(EpInfo)]),
         "ep_batch_sweep": (I, [P, P, I, I, P]),
         "ep_resource_batch": (I, [P, ctypes.c_double, ctypes.POINTER(I64), ctypes.POINTER(I64),
@@ -227,6 +229,14 @@ def ep_step(ctx, t, m, y_b, f_out=None):
     torch = _torch()
     return _check(_lib.ep_step(ctx, _ptr(t, torch.int64), m, _ptr(y_b, torch.float32),
                                _ptr(f_out, torch.float32, allow_none=True)))
+
+
+def ep_step_pass(ctx, m):
+    """EP_PASS_FLOAT32, EP_PASS_SPLIT or EP_PASS_BLOCKED: how ep_step forms F
+    for a batch of m rows."""
+    p = ctypes.c_int()
+    _check(_lib.ep_step_pass(ctx, m, ctypes.byref(p)))
+    return p.value
 
 
 def ep_predict(ctx, Z, n_z, out):

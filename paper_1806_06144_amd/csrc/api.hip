@@ -1616,6 +1616,16 @@ int ep_set_contraction(ep_ctx* c, int mode, int64_t block_bytes) {
     return EP_OK;
 }
 
+int ep_step_pass(ep_ctx* c, int64_t m, int* pass) {
+    g_err.clear();
+    if (!c || !pass) return fail(EP_EINVAL, "ctx or pass is NULL");
+    if (m < 1 || m > c->n) return fail(EP_EINVAL, "batch size m=%lld outside [1, n]", (long long)m);
+    *pass = use_blocked(c, nullptr, c->d) ? EP_PASS_BLOCKED
+            : use_split_step(c, m)        ? EP_PASS_SPLIT
+                                          : EP_PASS_FLOAT32;
+    return EP_OK;
+}
+
 int ep_sync(ep_ctx* c) {
     g_err.clear();
     if (!c) return fail(EP_EINVAL, "ctx is NULL");

@@ -56,6 +56,7 @@ def test_calls_on_null_context():
     assert ep.raw_call("ep_sync", None) == ep.EP_EINVAL
     assert ep.raw_call("ep_set_checks", None, 1) == ep.EP_EINVAL
     assert ep.raw_call("ep_timing_enable", None, 1) == ep.EP_EINVAL
+    assert ep.raw_call("ep_step_pass", None, 1, None) == ep.EP_EINVAL
     ep.raw_call("ep_destroy", None)
 
 

@@ -76,6 +76,7 @@ def test_setup_and_calls_without_room(problem):
     before = _free(torch)
     ctx, _ = ep.ep_setup(X, n, d, l, "gaussian", bw, len(r), 20, sub_idx=r)
     assert before - _free(torch) > 2 * GB             # the packed centres are held
+    assert ep.ep_step_pass(ctx, 700) == ep.EP_PASS_SPLIT
     want = calls(ctx)
     ep.ep_destroy(ctx)
     with Hold(torch, 3 * GB):                         # half of it is less than they need
@@ -83,6 +84,7 @@ def test_setup_and_calls_without_room(problem):
         ctx, _ = ep.ep_setup(X, n, d, l, "gaussian", bw, len(r), 20, sub_idx=r)
         try:
             assert before - _free(torch) < GB // 2
+            assert ep.ep_step_pass(ctx, 700) == ep.EP_PASS_FLOAT32
             got = calls(ctx)
         finally:
             ep.ep_destroy(ctx)
@@ -105,6 +107,7 @@ def test_split_operands_are_given_up_for_a_call(problem):
                 before = _free(torch)
                 P = _predict(ep, torch, ctx, Z, l)
                 assert _free(torch) - before > GB     # the packed centres went
+                assert ep.ep_step_pass(ctx, 700) == ep.EP_PASS_FLOAT32
                 assert rel(P[:600], want) < TOL_STEP
                 ep.ep_set_alpha(ctx, -a)              # (alpha itself stays in use)
                 P2 = _predict(ep, torch, ctx, Z[:600].contiguous(), l)

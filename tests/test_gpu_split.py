@@ -493,3 +493,55 @@ def test_second_step_keeps_its_precision():
             e.append(errs[1] / (EPS * S))
     print("second step in units of 2^-24 S", e)
     assert np.sqrt(np.mean(np.square(e))) <= 1.5
+
+
+# ---- which steps take the split pass -----------------------------------------
+
+def _pass(g, m):
+    import paper_1806_06144_amd as ep
+    return {ep.EP_PASS_FLOAT32: "float32", ep.EP_PASS_SPLIT: "split",
+            ep.EP_PASS_BLOCKED: "blocked"}[ep.ep_step_pass(g.ctx, m)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kernel,d,l,ms", [
+    # beyond 160 labels batches of more than 2048 rows keep the float32 pass
+    ("gaussian", 700, 200, [(300, "split"), (2049, "float32"), (300, "split"), (2048, "split")]),
+    ("gaussian", 700, 160, [(2049, "split"), (300, "split")]),
+    # Laplacian steps do beyond 2048 features
+    ("laplacian", 2049, 12, [(300, "float32"), (300, "float32")]),
+    ("laplacian", 2048, 12, [(300, "split"), (300, "split")]),
+    ("gaussian", 2049, 12, [(300, "split")]),
+    # and passes of at most 2^27 multiply-adds
+    ("gaussian", 699, 12, [(64, "split"), (30, "split")]), ("gaussian", 698, 12, [(64, "float32")]),
+])
+def test_steps_on_both_sides_of_a_line(kernel, d, l, ms):
+    """Steps on one context that change pass, and predictions (always split
+    here) between them, which read the planes of alpha that each step left."""
+    n, s, k = 3001, 150, 12
+    bw = bw32(1.3 if kernel == "gaussian" else 1.0)
+    rng = np.random.default_rng(d + l)
+    X = (rng.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    Y = np.eye(l, dtype=np.float32)[rng.integers(0, l, n)]
+    Z = (rng.standard_normal((400, d)) / np.sqrt(d)).astype(np.float32)
+    a_o = a0 = (rng.standard_normal((n, l)) / np.sqrt(n)).astype(np.float32)
+    r = rng.choice(n, s, replace=False)
+    st = oracle.setup(X, kernel_id(kernel), bw, s, k, r)
+    with Gpu(X, l, kernel, bw, s, k, r) as g:
+        g.set_alpha(a0)
+        for m, want in ms:
+            assert _pass(g, m) == want
+            t = rng.choice(n, m, replace=False)
+            F = g.step(t, Y[t])
+            a_o, F_o = oracle.step(st, a_o, t, Y[t])
+            assert rel(F, F_o) < TOL_STEP
+            P_o = oracle.predict(X.astype(np.float64), a_o, Z.astype(np.float64), kernel_id(kernel), bw)
+            assert rel(g.predict(Z), P_o) < TOL_STEP
+        assert rel(g.alpha() - a0, a_o - a0) < TOL_STEP
+        # the form that is asked for: the float32 order stays reachable beyond 160 labels
+        import paper_1806_06144_amd as ep
+        ep.ep_set_contraction(g.ctx, "fused")
+        gated = l > 160 or (kernel == "laplacian" and d > 2048)
+        assert _pass(g, 300) == ("float32" if gated else "split")
+        ep.ep_set_contraction(g.ctx, "blocked")
+        assert (_pass(g, 300) == "blocked") == (d % 4 == 0)
