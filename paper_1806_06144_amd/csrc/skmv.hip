@@ -592,6 +592,11 @@ constexpr int kWTiles = 8;                           // label tiles per workgrou
 constexpr int kWQ = 128;                             // queries per workgroup
 constexpr int kWSlotQuads = kWTiles * 3 * 64;
 
+// wg_barrier for all but the 12 most recent vector-memory operations.
+__device__ __forceinline__ void barrier_but_12() {
+    asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 __global__ void __launch_bounds__(kSThreads, 2) wmul_kernel(WmulArgs p) {
     __shared__ uintx4 ws0[kWSlotQuads];
     __shared__ uintx4 ws1[kWSlotQuads];
@@ -689,7 +694,7 @@ __global__ void __launch_bounds__(kSThreads, 2) wmul_kernel(WmulArgs p) {
             for (int b = 0; b < 2; ++b) oacc[j][b] += S & 1 ? -t[b] : t[b];
         }
         // the next group's weights, fetched a step ago, are in LDS for all
-        if (i + 2 < n) wg_barrier<12>();
+        if (i + 2 < n) barrier_but_12();
         else wg_barrier<0>();
     };
     if (n > 0) {

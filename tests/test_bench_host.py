@@ -59,3 +59,13 @@ def test_code_hash_ignores_comments_only():
     assert bench.code_text(src) == bench.code_text(same)
     assert bench.code_text(src) != bench.code_text(changed)
     assert "//" not in bench.code_text(src) and "/*" not in bench.code_text(src)
+
+
+def test_traffic_records_belong_to_the_current_kernels():
+    """Every committed HBM record was taken on the code of its kernel as it is
+    (comments aside), so that bench.py can report it."""
+    with open(os.path.join(ROOT, "profiles", "hbm_traffic.json")) as f:
+        rec = json.load(f)
+    assert rec
+    for key, entry in rec.items():
+        assert entry["source_sha"] == bench.kernel_source_sha(key.split(" | ")[1]), key
