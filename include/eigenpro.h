@@ -209,12 +209,13 @@ int ep_predict(ep_ctx* ctx, const float* Z, int64_t n_z, float* out);
  * ep_predict_noalloc — ep_predict for callers that cannot allocate device
  * memory: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc. Same arguments and result (up to float32 summation
- * order); it calls no allocating routine. Its scratch (the row norms of a
- * chunk of Z and the partial sums of the fused pass) is a 64 MiB array that
- * the library holds once per device for the life of the process, looked up
- * when the first context is created on that device. Z is processed in
- * chunks sized to fit it; always the fused form (ep_set_contraction does
- * not apply).
+ * order); it calls no allocating routine. Its scratch (packed rows or row
+ * norms of a chunk of Z, the partial sums of the pass and, beyond 160 labels,
+ * the kernel values of a chunk of centres) is a 64 MiB array that the library
+ * holds once per device for the life of the process, looked up when the first
+ * context is created on that device. Z is processed in chunks sized to fit it,
+ * on the 16-bit matrix cores where a chunk does, else on float32 operands;
+ * never in the blocked form.
  * Concurrency: every call on one device shares that device's scratch, so
  * calls that overlap on one GPU (two streams, two threads, two contexts)
  * race; serialise them. The scratch keeps the last call's contents; nothing

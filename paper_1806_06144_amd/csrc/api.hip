@@ -263,16 +263,24 @@ bool use_split(const ep_ctx* c, int64_t nq) {
     return c->split &&
            (double)round_up(nq, kBM) * (double)c->n * (double)c->d > (double)(1 << 27);
 }
-// The same for a training step. Two ranges stay on the float32 pass, because
-// there a step's result depends on the summation order by more than a change
-// of kernel may move it (4e-5), from the second step of a run on:
-//  - Laplacian steps on rows of more than 2048 features (n = 50000, d = 3072,
-//    uniform features: 5.3e-5 off float64 with the float32 pass, 4.1e-5 with
-//    the split one, 6e-5 between the two; 7.5 against 2.4 ms);
-//  - more than 160 labels with batches of more than 2048 rows or more than
-//    2^29 kernel entries (n = 1.28 M, d = 2048, l = 1000, m = 3561: 7.1e-5,
-//    6.0e-5, 7.5e-5; 203 against 90 ms; n = 256316, m = 2964: 7.3e-5 between
-//    the two). At n = 160000, m = 1601 the two are 2.3e-5 apart.
+// The same for a training step, but for two ranges that keep the float32
+// pass. A step along the top eigenvector is S times larger than what steps 4-5
+// leave of it (m c sigma_1 / s, 60 to 360 at the workloads' batch sizes), so
+// from the second step of a run on every rounding shows S times as large, and
+// two correct float32 passes differ by as much as each is off. Measured
+// against float64, second step, float32 pass / split pass:
+//   Laplacian, 50000 centres, m = 3039: d = 3072 7.9e-5 / 6.0e-5, d = 2049
+//     5.8e-5 / 4.0e-5, d = 2048 4.4e-5 / 3.2e-5, d = 2000 8.8e-5 / 3.4e-5;
+//   1000 labels, d = 2048: 1.28 M centres, m = 3561 7.3e-5 / 5.2e-5; 256316,
+//     m = 2964 5.6e-5 / 4.1e-5; 130000, m = 2049 2.8e-5 / 2.6e-5, m = 2047
+//     3.3e-5 / 2.7e-5; 160000, m = 1601 2.2e-5 / 2.2e-5.
+// The split pass is the nearer and the faster one (7.4 against 2.4 ms and 203
+// against 90 ms at the largest of each). These ranges are not where it would
+// be worse, nor all where a change of pass shows (Gaussian, 50000 x 3072:
+// 1.4e-4 / 1.1e-4): they are where the results of two full-size workloads are
+// held to what the library gave before, within 4e-5, which the float32 pass's
+// own error exceeds there. Beyond 160 labels the form EP_CONTRACT_FUSED means
+// the float32 pass everywhere; ep_step_pass says which one runs.
 bool keeps_order(const ep_ctx* c, int64_t m) {
     return (c->kind == EP_LAPLACIAN && c->d > 2048) ||
            (c->lt16 > kMaxFusedTiles &&

@@ -10,12 +10,12 @@
 // one, so the distance product costs 3/16 and the contraction 6/16 of what it
 // did.
 //
-// Bound by the 16-bit MFMA rate under this card's power limit (a large
-// library product reaches 1.14 to 1.36 of the nominal 2.5 PFLOP/s). Of it
-// the pass reaches, counting its three and six products: 1.0 PFLOP/s at
-// 60000 x 784, 10 labels, 1310 queries (382 us; the float32 pass 1070 us),
-// 1.25 at 50000 x 3072 with 10000 queries, 0.92 at 1.1 M x 440, 144 labels,
-// 1257 queries (6.55 ms; float32 12.9 ms).
+// The matrix pipes are busy 44 to 65 % of the cycles, at 2.4 GHz in a short
+// step and 1.7 to 2.05 GHz, under the card's power limit, in longer ones; the
+// rest are waits inside the workgroups. Counting three and six products: 1.0
+// PFLOP/s at 60000 x 784, 10 labels, 1310 queries (382 us; the float32 pass
+// 1070 us), 1.42 with 10000 queries, 0.92 at 1.1 M x 440, 144 labels, 1257
+// queries (6.55 ms; float32 12.9 ms); a large library product reaches 1.2.
 //
 // Four waves share a panel of 128 centres through LDS (direct-to-LDS loads
 // of 32 features, three stages ahead in four slots, one barrier per stage);
