@@ -545,3 +545,29 @@ def test_steps_on_both_sides_of_a_line(kernel, d, l, ms):
         assert _pass(g, 300) == ("float32" if gated else "split")
         ep.ep_set_contraction(g.ctx, "blocked")
         assert (_pass(g, 300) == "blocked") == (d % 4 == 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("l", [6, 200])
+@pytest.mark.parametrize("e", [-60, -50, -49, 40])
+def test_features_scaled_by_a_power_of_two(e, l):
+    """The same kernel values from features and bandwidth scaled by 2^e, down
+    to rows whose squares are the smallest normal floats, where the rows share
+    one scale (below 2^-49) and lo has 24 bits under the largest element."""
+    n, d, n_z, bw = 128 * 300 + 5, 64, 70, 9.0
+    rng = np.random.default_rng(1)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    Z = rng.standard_normal((n_z, d)).astype(np.float32)
+    a = rng.standard_normal((n, l)).astype(np.float32)
+    f = np.float32(2.0 ** e)
+    P = []
+    for s in (np.float32(1), f):
+        with Gpu(X * s, l, "gaussian", float(np.float32(bw) * s), 20, 2, np.arange(20)) as g:
+            g.set_alpha(a)
+            P.append(g.predict(Z * s))
+    # (the scaling is exact; below 2^-49 the low planes of small elements end
+    # 2^-25 under the row's largest, a few roundings of the distance)
+    assert rel(P[1], P[0]) < 1e-6
+    P_o = oracle.predict(X.astype(np.float64), a.astype(np.float64), Z.astype(np.float64),
+                         oracle.GAUSSIAN, bw)
+    assert np.max(np.abs(P[1] - P_o) / _bound(X, Z, a, "gaussian", bw)) <= 1.0
