@@ -184,6 +184,8 @@ def _rows(law, d, n, rng):
     if law.startswith("column"):
         value, at = law.split()[1:]
         x[:, int(float(at) * (d - 1))] = np.float32(value)
+    if law == "spread":          # features of very different size
+        x *= np.exp2(-np.random.default_rng(d).integers(0, 21, d)).astype(np.float32)
     if law == "sparse":          # few features, so no sum evens the rounding out
         x *= rng.random((n, d)) < 12.0 / d
     return x.astype(np.float32)
@@ -191,7 +193,7 @@ def _rows(law, d, n, rng):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", [16, 64, 784])
-@pytest.mark.parametrize("law", ["normal", "two", "sparse", "column 64.0312 0", "column 64.0312 1",
+@pytest.mark.parametrize("law", ["normal", "two", "spread", "sparse", "column 64.0312 0", "column 64.0312 1",
                                  "column 33.015 0.5", "column 65.03 0", "near"])
 def test_distances_are_as_good_as_float32(law, d):
     """Squared distances, read off the kernel values of single centres, of
@@ -222,11 +224,11 @@ def test_distances_are_as_good_as_float32(law, d):
             dot = (dot + z[:, j, None].astype(np.float64) * x[None, :, j]).astype(np.float32)
         return (zn.astype(np.float32)[:, None] + xn.astype(np.float32)[None]) - np.float32(2) * dot
 
-    # distance of the packed rows (no element here is below 2^-16 of its row's
-    # largest by more than the fp16 range, so the row's scale does not matter)
+    # distance of the packed rows
     def packed(r):
-        h = r.astype(np.float16).astype(np.float32)
-        return h.astype(np.float64) + (r - h).astype(np.float16)
+        e = np.exp2(14 - np.floor(np.log2(np.abs(r).max(1, keepdims=True) + 1e-30))).astype(np.float32)
+        h = (r * e).astype(np.float16).astype(np.float32)
+        return (h.astype(np.float64) + (r * e - h).astype(np.float16)) / e
 
     p2 = np.stack([((packed(z) - r) ** 2).sum(1) for r in packed(x)], 1)
     bw = bw32(np.sqrt(d2[pair].mean() / 8))
